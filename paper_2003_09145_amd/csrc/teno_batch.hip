@@ -56,11 +56,10 @@ struct BatchArgs {
 // path's reduction) and its physicality.
 __device__ __forceinline__ double cell_speed(const double* q, double gamma, bool* bad) {
     const double rho = q[0];
-    const double rrho = rcp_nr(rho);
-    const double u = cr_div_r(q[1], rho, rrho);
+    const double u = cr_div_p(q[1], rho);
     const double ke = 0.5 * (q[1] * u);
     const double p = (gamma - 1.0) * (q[2] - ke);
-    const double cs = cr_sqrt(cr_div_r(gamma * p, rho, rrho));
+    const double cs = cr_sqrt(cr_div_p(gamma * p, rho));
     *bad = !(rho > 0.0) || !(p > 0.0) || !isfinite(cs);
     return fabs(u) + cs;
 }
@@ -163,7 +162,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
                 double hh = 0.0;
                 if (st_prev[b] == 0 && A.t[b] < A.t_end) {
                     const double a0 = a_cur[b];
-                    hh = cr_div_r(A.cfl * dxb, a0, rcp_nr(a0));
+                    hh = cr_div_p(A.cfl * dxb, a0);
                     if (A.t[b] + hh > A.t_end) hh = A.t_end - A.t[b];
                 }
                 A.dt[b] = hh;
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
             if (active) {
                 if (A.t[b] < A.t_end) {
                     const double a0 = a_cur[b];
-                    h = cr_div_r(A.cfl * dxb, a0, rcp_nr(a0));
+                    h = cr_div_p(A.cfl * dxb, a0);
                     if (A.t[b] + h > A.t_end) h = A.t_end - A.t[b];
                 } else {
                     active = false;
@@ -184,12 +183,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
         double speed = 0.0;
         if (active) {
             const int64_t cell = A.off[b] + phi - 1;
-            const double rdx = rcp_nr(dxb);
             double qn[NC];
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const double diff = fhs[c * 64 + lane] - fhs[c * 64 + lane - 1];
-                const double r = 0.0 - cr_div_r(diff, dxb, rdx);
+                const double r = 0.0 - cr_div_p(diff, dxb);
                 const size_t at = (size_t)c * A.total + cell;
                 double v;
                 if (A.stage == 0) {

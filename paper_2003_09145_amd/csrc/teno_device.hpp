@@ -71,6 +71,12 @@ __device__ __forceinline__ bool in_safe_range(double v) {
     return av >= 0x1p-900 && av <= 0x1p900;
 }
 
+// b in [2^-400, 2^400): one unsigned compare of the high word, which also
+// turns away negative values, zeros, infinities and NaN.
+__device__ __forceinline__ bool in_mid_range(double b) {
+    return (uint32_t)(__double_as_longlong(b) >> 32) - 0x26f00000u < 0x58f00000u - 0x26f00000u;
+}
+
 // Sufficient test that q = RN(a / b) given r = RN(a - q b): |a/b - q| <
 // ulp(q)/2 with both neighbours of q one ulp away makes q the nearest
 // double.  q = mq 2^eq with |mq| in (1/2, 1) excludes zero, powers of two,
@@ -114,16 +120,19 @@ __device__ __forceinline__ double cr_sqrt_exact(double x) {
     return (r <= sg) ? sn : s;
 }
 
-// sqrt(x) correctly rounded.  In the safe range the root comes from the
+// sqrt(x) correctly rounded.  For x in [2^-400, 2^400) the root comes from the
 // hardware reciprocal square root refined by one Goldschmidt and two Newton
-// steps (no scaling is needed there) and is accepted when
-// |x - s^2| < ulp(s) (s - ulp(s)): a root error of half an ulp or more would
-// make |x - s^2| >= ulp(s) (s - ulp(s)/4), and rounding is monotone, so the
-// accepted s is the nearest double (s not a power of two, both neighbours one
-// ulp away; the bound is exact and normal).  Everything else takes the exact
-// neighbour test on the compiler's root.
+// steps (no scaling is needed there).  A root that the test below does not
+// certify takes the exact neighbour test on the compiler's root.
 // Fast phase: *s is the refined root (for x outside the safe range, any
 // value); true when it is certified.  The exact phase is cr_sqrt_exact.
+//
+// The certificate is a rounding test: with r = x - s^2 (exact) and h = (1 / 2s)
+// (1 + d), |d| < 2^-44 (the hardware's reciprocal root has a relative error
+// below 2^-23, and one Goldschmidt step squares it), the distance of the root
+// from s is r h to a relative 2^-43, so s + r h (1 + 2^-40) rounding to s puts
+// the root nearer to s than to any other double (the spacing below a power of
+// two included).
 __device__ __forceinline__ bool sqrt_fast(double x, double* sout) {
     const double y = __builtin_amdgcn_rsq(x);
     double s = x * y;
@@ -136,11 +145,8 @@ __device__ __forceinline__ bool sqrt_fast(double x, double* sout) {
     d = __builtin_fma(-s, s, x);
     s = __builtin_fma(d, h, s);
     const double r = __builtin_fma(-s, s, x);
-    int es;
-    const double ms = frexp(s, &es);
-    const double u = ldexp(1.0, es - 53);  // ulp(s)
     *sout = s;
-    return (x >= 0x1p-900 && x <= 0x1p900) && fabs(r) < ldexp(s - u, es - 53) && ms > 0.5;
+    return in_mid_range(x) && __builtin_fma(r * (1.0 + 0x1p-40), h, s) == s;
 }
 __device__ __forceinline__ double cr_sqrt(double x) {
     double s;
@@ -157,54 +163,66 @@ __device__ __forceinline__ double rcp_nr(double b) {
     return __builtin_fma(r, e, r);
 }
 
-// Correctly rounded a / b from rb = rcp_nr(b): q0 = a rb, one Markstein step
-// q1 = q0 + (a - q0 b) rb (faithful), then the exact-remainder correction of
-// cr_div.  Outside the safe range it defers to cr_div.
-//
-// Split in two phases so that several independent divisions share one
-// (rarely taken) correction branch: div_r_fast forms q1 and its remainder and
-// reports whether the fast test already certifies q1; div_r_fix corrects a
-// quotient the test did not certify.
-__device__ __forceinline__ bool div_r_fast(double a, double b, double rb, double* q, double* r) {
-    const double q0 = a * rb;
-    const double e = __builtin_fma(-q0, b, a);
-    *q = __builtin_fma(e, rb, q0);
-    *r = __builtin_fma(-*q, b, a);  // exact in the safe range
-    return quotient_is_nearest(*q, b, *r);
+// Correctly rounded reciprocal and quotients without a test per quotient (P.
+// Markstein, "Computation of elementary functions on the IBM RISC System/6000
+// processor", IBM J. Res. Dev. 34, 1990):
+//  - a Newton step y + y (1 - b y) from a y within one ulp of 1 / b rounds to
+//    RN(1 / b) unless every mantissa bit of b is set (rcp_nr is within 0.6 ulp:
+//    the hardware estimate's 2^-23, squared twice, plus one rounding);
+//  - with y = RN(1 / b) and q within one ulp of a / b, q - (q b - a) y rounds
+//    to RN(a / b) (the remainder is exact).
+// rcp_exact reports whether y is certified: b in [2^-400, 2^400] and its low
+// mantissa word not all ones.  quot takes a certified y and an a that is zero
+// or within [2^-600, 2^600] in magnitude (quot_ok, and the caller's bound), so
+// that no remainder under- or overflows; the negated remainder keeps a zero's
+// sign.  Everything else takes cr_div.  Against the test of every quotient's
+// remainder with half the spacing of doubles this took 3 of 11 instructions
+// off a quotient, 6 of 16 off a reciprocal, and it does not fail for zero
+// dividends and powers of two (128 x 512 Rayleigh-Taylor: -6% per step; with
+// the 4 beta form below: -6% per 256^3 step, 1326 -> 1180 VALU instructions
+// per wave of 63 faces).
+__device__ __forceinline__ bool rcp_exact(double b, double* y) {
+    const double r = rcp_nr(b);
+    *y = __builtin_fma(r, __builtin_fma(-b, r, 1.0), r);
+    return in_mid_range(b) && (uint32_t)__double_as_longlong(b) != 0xffffffffu;
 }
-__device__ __forceinline__ double div_r_fix(double a, double b, double q, double r) {
-    if (!(in_safe_range(a) && in_safe_range(b) && in_safe_range(q))) return cr_div(a, b);
-    if (r == 0.0) return q;
-    const bool up = (r > 0.0) == (b > 0.0);
-    const double qn = step_toward(q, up);
-    const double h = 0.5 * ((qn - q) * b);
-    const double ar = fabs(r), ah = fabs(h);
-    if (ar > ah) return qn;
-    if (ar == ah) return (__double_as_longlong(q) & 1ll) ? qn : q;
-    return q;
+__device__ __forceinline__ double quot(double a, double b, double y) {
+    const double q0 = a * y;
+    const double q1 = __builtin_fma(-__builtin_fma(q0, b, -a), y, q0);
+    return __builtin_fma(-__builtin_fma(q1, b, -a), y, q1);
 }
-__device__ __forceinline__ double cr_div_r(double a, double b, double rb) {
-    double q, r;
-    if (div_r_fast(a, b, rb, &q, &r)) return q;
-    return div_r_fix(a, b, q, r);
-}
-// q[i] = a[i] / b correctly rounded for N independent dividends.
+// Lower bound of quot's dividends (the caller bounds them from above).
+__device__ __forceinline__ bool quot_ok(double a) { return !(fabs(a) < 0x1p-600) || a == 0.0; }
+
+// q[i] = a[i] / b correctly rounded for N independent dividends, from y =
+// RN(1 / b) (yok: certified, see rcp_exact): one correction branch for all.
 template <int N>
-__device__ __forceinline__ void cr_div_r_n(const double (&a)[N], double b, double rb,
-                                           double (&q)[N]) {
-    double r[N];
-    bool ok[N];
-    bool all = true;
+__device__ __forceinline__ void cr_div_n(const double (&a)[N], double b, double y, bool yok,
+                                         double (&q)[N]) {
+    bool ok = yok;
+    double big = 0.0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        ok[i] = div_r_fast(a[i], b, rb, &q[i], &r[i]);
-        all = all && ok[i];
+        q[i] = quot(a[i], b, y);
+        ok = ok && quot_ok(a[i]);
+        big = (i == 0) ? fabs(a[i]) : big + fabs(a[i]);
     }
-    if (!all) {
+    if (!(ok && big < 0x1p600)) {
 #pragma unroll
-        for (int i = 0; i < N; ++i)
-            if (!ok[i]) q[i] = div_r_fix(a[i], b, q[i], r[i]);
+        for (int i = 0; i < N; ++i) q[i] = cr_div(a[i], b);
     }
+}
+
+// a / b and 1 / b correctly rounded for positive b.
+__device__ __forceinline__ double cr_div_p(double a, double b) {
+    double y;
+    if (rcp_exact(b, &y) && quot_ok(a) && fabs(a) < 0x1p600) return quot(a, b, y);
+    return cr_div(a, b);
+}
+__device__ __forceinline__ double cr_rcp(double b) {
+    double y;
+    if (rcp_exact(b, &y)) return y;
+    return cr_div(1.0, b);
 }
 
 // TENO weights of eq 2.15 for each cutoff mask, omega_k = delta_k c_k / D with
@@ -242,6 +260,7 @@ struct DecisionConsts {
     int32_t nthr;          // B_u - B_l
     int32_t literal;       // 1: evaluate every decision with the literal formula
     int32_t need_m;        // 1: the ladder index is wanted (decision dumps)
+                           // (either switches the smooth-stencil bound off)
     int32_t pad_;
     // Smooth-stencil bound: when tau <= smooth_t (min_k beta_k + eps), every
     // chi~_k = tau / (beta_k + eps) is at most smooth_t (to rounding), so each
@@ -249,7 +268,9 @@ struct DecisionConsts {
     // least 1 / (1 + 2 (1 + smooth_t)^6), which the host chooses above the
     // largest cutoff ct_hi: all three stencils are kept, whatever the ladder
     // index.  Negative: no such bound (never satisfied).
-    double smooth_t;
+    // (The kernels test 4 tau against 4 min_k beta_k: smooth_te = 4 smooth_t eps.)
+    double smooth_t, smooth_te;
+    double eps4;           // 4 eps
     // host products of the margins below: ct_hi (1 + margin) and ct_lo (1 -
     // margin) (kept out of the kernels' loops, where the compiler would
     // re-form them for every characteristic field)
@@ -271,7 +292,8 @@ constexpr double kDecisionMargin = 0x1p-40;
 // df_{j+1/2}^2 + df_{j-1/2}^2), eta_{i+1/2} = their minimum, m = 1 - min(1,
 // eta / C_r), g = (1 - m)^4 (1 + 4 m), beta = alpha_1 - alpha_2 (1 - g),
 // C_T = 10^-floor(beta).  Operation order of the oracle; *k = floor(beta).
-__device__ __forceinline__ double teno5a_cutoff(const SchemeParams& S, double a, double b,
+template <class SP>
+__device__ __forceinline__ double teno5a_cutoff(const SP& S, double a, double b,
                                                 double c, double d, double e, int* k) {
     const double df0 = b - a, df1 = c - b, df2 = d - c, df3 = e - d;
     // 2 x and 4 x are exact, so the fused forms below round exactly as the
@@ -298,10 +320,18 @@ __device__ __forceinline__ double teno5a_cutoff(const SchemeParams& S, double a,
 
 // A5: the launch runs TENO5-A (scheme 3); its cutoff code is compiled only
 // into the A5 instantiations, so the other schemes' kernels do not carry it.
-template <bool A5>
-__device__ __forceinline__ uint32_t teno5_decide_literal(const SchemeParams& S, double beta0,
-                                                      double beta1, double beta2, double a,
+template <bool A5, class SP>
+__device__ __forceinline__ uint32_t teno5_decide_literal(const SP& S, double a,
                                                       double b, double c, double d, double e) {
+    const double s01 = __builtin_fma(-2.0, b, a) + c;
+    const double s02 = __builtin_fma(3.0, c, __builtin_fma(-4.0, b, a));
+    const double s11 = __builtin_fma(-2.0, c, b) + d;
+    const double s12 = b - d;
+    const double s21 = __builtin_fma(-2.0, d, c) + e;
+    const double s22 = __builtin_fma(3.0, c, __builtin_fma(-4.0, d, e));
+    const double beta0 = __builtin_fma(kB13_12 * s01, s01, kB1_4 * (s02 * s02));
+    const double beta1 = __builtin_fma(kB13_12 * s11, s11, kB1_4 * (s12 * s12));
+    const double beta2 = __builtin_fma(kB13_12 * s21, s21, kB1_4 * (s22 * s22));
     const double tau = fabs(beta2 - beta0);
     const double t0 = cr_div(tau, beta0 + S.eps);
     const double t1 = cr_div(tau, beta1 + S.eps);
@@ -345,126 +375,145 @@ __device__ __forceinline__ uint32_t teno5_decide_literal(const SchemeParams& S, 
     return (uint32_t)m | (mask << 5);
 }
 
-// One scalar TENO5 reconstruction of the face value from (a..e) =
-// (f_{i-2} .. f_{i+2}): smoothness indicators (eq 2.9-2.12), scale
-// separation (eq 2.8, 2.13), cutoff (eq 2.14) with C_T from the LAD mapping
-// (eq 3.1-3.4), weights (eq 2.15) and combination (eq 2.4-2.7).
+// Decision of a stencil (a..e) = (f_{i-2} .. f_{i+2}) that the smooth-stencil
+// bound does not settle: m | (mask << 5).
 //
 // The cutoff flags and the ladder index are discrete functions of the
 // literal formula.  They are first evaluated with approximate reciprocals;
 // if any decision value lies within kDecisionMargin of its threshold (or is
 // not finite) the lane re-evaluates the literal formula, so the decisions
-// equal the literal ones exactly.  The flux itself is the literal
-// combination with the eq 2.15 weights of the chosen mask.
-// *code receives m | (mask << 5).
-template <bool A5>
-__device__ __forceinline__ double teno5_rec_fast(const SchemeParams& S, const DecisionConsts& K,
-                                                 const double* __restrict__ omega_lds,
-                                                 double a, double b, double c, double d,
-                                                 double e, uint32_t* code) {
+// equal the literal ones exactly.  b4_k = 4 beta_k.  SP, KP: SchemeParams and
+// DecisionConsts, in any address space.
+template <bool A5, class SP, class KP>
+__device__ __forceinline__ uint32_t teno5_decide(const SP& S, const KP& K,
+                                                 double b40, double b41, double b42, double a,
+                                                 double b, double c, double d, double e) {
+    bool sure = K.literal == 0;
+    uint32_t m = 0, mask = 7u;
+    if (sure) {
+        // Approximate gamma_k (eq 2.8) from approximate chi~_k = tau / (beta_k + eps).
+        const double tau4 = fabs(b42 - b40);
+        const double t0 = tau4 * rcp_nr(b40 + K.eps4);
+        const double t1 = tau4 * rcp_nr(b41 + K.eps4);
+        const double t2 = tau4 * rcp_nr(b42 + K.eps4);
+        double y, y2;
+        y = 1.0 + t0;
+        y2 = y * y;
+        const double g0 = (y2 * y2) * y2;
+        y = 1.0 + t1;
+        y2 = y * y;
+        const double g1 = (y2 * y2) * y2;
+        y = 1.0 + t2;
+        y2 = y * y;
+        const double g2 = (y2 * y2) * y2;
+        const double sum = (g0 + g1) + g2;
+        // chi_k = g_k / sum against the extreme cutoffs: a flag that is the
+        // same for every rung of the ladder needs no ladder index.  TENO5-A
+        // evaluates its cutoff exactly and uses it for both bounds.
+        double chi_hi = K.ct_hi, chi_lo = K.ct_lo;
+        if (A5) {
+            int kA;
+            chi_hi = chi_lo = teno5a_cutoff(S, a, b, c, d, e, &kA);
+            m = (uint32_t)kA;
+        }
+        const double hi = (A5 ? chi_hi * (1.0 + kDecisionMargin) : K.hi_fac) * sum;
+        const double lo = (A5 ? chi_lo * (1.0 - kDecisionMargin) : K.lo_fac) * sum;
+        const bool k0 = g0 >= hi, k1 = g1 >= hi, k2 = g2 >= hi;
+        const bool c0 = g0 < lo, c1 = g1 < lo, c2 = g2 < lo;
+        sure = isfinite(sum) && (k0 || c0) && (k1 || c1) && (k2 || c2);
+        mask = (k0 ? 1u : 0u) | (k1 ? 2u : 0u) | (k2 ? 4u : 0u);
+        if (S.scheme == 0 && (K.need_m || !sure)) {
+            // ladder index from approximate x and theta.  A NaN t_k makes
+            // sum NaN, which already sends the lane to the literal
+            // formula; the clamp keeps the table index in range for any x.
+            const double x = fmax(fmax(t0, t1), t2);
+            const double y = rcp_nr(__builtin_fma(x, K.inv_h, 1.0)) * K.nthr_d;
+            const double fl = floor(y);
+            const double fr = y - fl;
+            bool msure = K.nthr == 0 || (isfinite(x) && fr > K.ymarg && fr < 1.0 - K.ymarg);
+            m = (uint32_t)S.Bl + (uint32_t)(int)fmin(fmax(fl, 0.0), K.nthr_d);
+            // cut form of theta: x certainly over H gives B_l; x within
+            // the margin of H takes the literal formula
+            if (x > K.h_hi) {
+                m = (uint32_t)S.Bl;
+                msure = true;
+            } else if (x >= K.h_lo) {
+                msure = false;
+            }
+            if (!sure) {
+                const double ct = kLadder[m];
+                const double rs = rcp_nr(sum);
+                const double x0 = g0 * rs, x1 = g1 * rs, x2 = g2 * rs;
+                const double band = kDecisionMargin * ct;
+                sure = isfinite(sum) && fabs(x0 - ct) > band && fabs(x1 - ct) > band &&
+                       fabs(x2 - ct) > band;
+                mask = (x0 < ct ? 0u : 1u) | (x1 < ct ? 0u : 2u) | (x2 < ct ? 0u : 4u);
+            }
+            sure = sure && msure;
+        }
+    }
+    if (sure) return m | (mask << 5);
+    return teno5_decide_literal<A5>(S, a, b, c, d, e);
+}
+
+// One scalar TENO5 reconstruction of the face value from (a..e) =
+// (f_{i-2} .. f_{i+2}): smoothness indicators (eq 2.9-2.12), scale
+// separation (eq 2.8, 2.13), cutoff (eq 2.14) with C_T from the LAD mapping
+// (eq 3.1-3.4), weights (eq 2.15) and combination (eq 2.4-2.7).  The flux is
+// the literal combination with the eq 2.15 weights of the mask that the
+// decision chose.  *code receives m | (mask << 5).
+//
+// Four times the smoothness indicators: with b4_k = (13/3 s) s + t t the
+// product by 1/4 goes, and the factor 4 is exact.  4 tau < smooth_t (4
+// min_k beta_k) + 4 smooth_t eps is one minimum, one fused multiply-add and one
+// compare; the strict compare turns an overflow away, a NaN beta_k (it
+// needs a NaN stencil value, which makes beta_0 or beta_2 NaN too) a NaN tau.
+struct Teno5Beta {
+    double b0, b1, b2;  // 4 beta_k
+};
+__device__ __forceinline__ Teno5Beta teno5_beta4(double a, double b, double c, double d, double e) {
     // sums of products as fused multiply-adds, in the oracle's order; a - 2 b
     // and a - 4 b are single roundings either way (2 b and 4 b are exact for
     // |b| below 2^1021), so they are fused here too
+    constexpr double k13_3 = 4.0 * kB13_12;
     const double s01 = __builtin_fma(-2.0, b, a) + c;
     const double s02 = __builtin_fma(3.0, c, __builtin_fma(-4.0, b, a));
     const double s11 = __builtin_fma(-2.0, c, b) + d;
     const double s12 = b - d;
     const double s21 = __builtin_fma(-2.0, d, c) + e;
     const double s22 = __builtin_fma(3.0, c, __builtin_fma(-4.0, d, e));
-    const double beta0 = __builtin_fma(kB13_12 * s01, s01, kB1_4 * (s02 * s02));
-    const double beta1 = __builtin_fma(kB13_12 * s11, s11, kB1_4 * (s12 * s12));
-    const double beta2 = __builtin_fma(kB13_12 * s21, s21, kB1_4 * (s22 * s22));
-
-    uint32_t cd;
-    if (S.scheme == 2) {
-        cd = 7u << 5;
-    } else {
-        bool sure = K.literal == 0;
-        uint32_t m = 0, mask = 7u;
-        const double tau = fabs(beta2 - beta0);
-        const double be0 = beta0 + S.eps, be1 = beta1 + S.eps, be2 = beta2 + S.eps;
-        // Smooth test tau <= smooth_t (min_k beta_k + eps), one compare per
-        // stencil: x -> RN(x + eps) and x -> RN(smooth_t x) are monotone
-        // (smooth_t > 0; a negative smooth_t fails every form), so the rounded
-        // bound at the smallest beta_k is the smallest of the three bounds.
-        // A NaN beta_k fails its compare, and it needs a NaN stencil value,
-        // which makes beta_0 or beta_2 NaN and so tau NaN as well.
-        const bool smooth = tau <= K.smooth_t * be0 && tau <= K.smooth_t * be1 &&
-                            tau <= K.smooth_t * be2;
-        if (sure && K.need_m == 0 && smooth) {
-            // smooth stencil: all kept (no reciprocal, no gamma_k)
-        } else if (sure) {
-            // Approximate gamma_k (eq 2.8) from approximate chi~_k = tau / (beta_k + eps).
-            const double t0 = tau * rcp_nr(be0);
-            const double t1 = tau * rcp_nr(be1);
-            const double t2 = tau * rcp_nr(be2);
-            double y, y2;
-            y = 1.0 + t0;
-            y2 = y * y;
-            const double g0 = (y2 * y2) * y2;
-            y = 1.0 + t1;
-            y2 = y * y;
-            const double g1 = (y2 * y2) * y2;
-            y = 1.0 + t2;
-            y2 = y * y;
-            const double g2 = (y2 * y2) * y2;
-            const double sum = (g0 + g1) + g2;
-            // chi_k = g_k / sum against the extreme cutoffs: a flag that is the
-            // same for every rung of the ladder needs no ladder index.  TENO5-A
-            // evaluates its cutoff exactly and uses it for both bounds.
-            double chi_hi = K.ct_hi, chi_lo = K.ct_lo;
-            if (A5) {
-                int kA;
-                chi_hi = chi_lo = teno5a_cutoff(S, a, b, c, d, e, &kA);
-                m = (uint32_t)kA;
-            }
-            const double hi = (A5 ? chi_hi * (1.0 + kDecisionMargin) : K.hi_fac) * sum;
-            const double lo = (A5 ? chi_lo * (1.0 - kDecisionMargin) : K.lo_fac) * sum;
-            const bool k0 = g0 >= hi, k1 = g1 >= hi, k2 = g2 >= hi;
-            const bool c0 = g0 < lo, c1 = g1 < lo, c2 = g2 < lo;
-            sure = isfinite(sum) && (k0 || c0) && (k1 || c1) && (k2 || c2);
-            mask = (k0 ? 1u : 0u) | (k1 ? 2u : 0u) | (k2 ? 4u : 0u);
-            if (S.scheme == 0 && (K.need_m || !sure)) {
-                // ladder index from approximate x and theta.  A NaN t_k makes
-                // sum NaN, which already sends the lane to the literal
-                // formula; the clamp keeps the table index in range for any x.
-                const double x = fmax(fmax(t0, t1), t2);
-                const double y = rcp_nr(__builtin_fma(x, K.inv_h, 1.0)) * K.nthr_d;
-                const double fl = floor(y);
-                const double fr = y - fl;
-                bool msure =
-                    K.nthr == 0 || (isfinite(x) && fr > K.ymarg && fr < 1.0 - K.ymarg);
-                m = (uint32_t)S.Bl + (uint32_t)(int)fmin(fmax(fl, 0.0), K.nthr_d);
-                // cut form of theta: x certainly over H gives B_l; x within
-                // the margin of H takes the literal formula
-                if (x > K.h_hi) {
-                    m = (uint32_t)S.Bl;
-                    msure = true;
-                } else if (x >= K.h_lo) {
-                    msure = false;
-                }
-                if (!sure) {
-                    const double ct = kLadder[m];
-                    const double rs = rcp_nr(sum);
-                    const double x0 = g0 * rs, x1 = g1 * rs, x2 = g2 * rs;
-                    const double band = kDecisionMargin * ct;
-                    sure = isfinite(sum) && fabs(x0 - ct) > band && fabs(x1 - ct) > band &&
-                           fabs(x2 - ct) > band;
-                    mask = (x0 < ct ? 0u : 1u) | (x1 < ct ? 0u : 2u) | (x2 < ct ? 0u : 4u);
-                }
-                sure = sure && msure;
-            }
-        }
-        cd = m | (mask << 5);
-        if (!sure) cd = teno5_decide_literal<A5>(S, beta0, beta1, beta2, a, b, c, d, e);
-    }
-    *code = cd;
-    const uint32_t mask = cd >> 5;
+    Teno5Beta B;
+    B.b0 = __builtin_fma(k13_3 * s01, s01, s02 * s02);
+    B.b1 = __builtin_fma(k13_3 * s11, s11, s12 * s12);
+    B.b2 = __builtin_fma(k13_3 * s21, s21, s22 * s22);
+    return B;
+}
+__device__ __forceinline__ bool teno5_smooth(double smooth_t, double smooth_te, const Teno5Beta& B) {
+    return fabs(B.b2 - B.b0) <
+           __builtin_fma(smooth_t, __builtin_fmin(__builtin_fmin(B.b0, B.b1), B.b2), smooth_te);
+}
+// Combination of the candidate fluxes with the weights w (eq 2.4-2.7).
+__device__ __forceinline__ double teno5_combine(double w0, double w1, double w2, double a, double b,
+                                                double c, double d, double e) {
     const double f0 = __builtin_fma(kC11_6, c, __builtin_fma(kC1_3, a, -kC7_6 * b));
     const double f1 = __builtin_fma(kC1_3, d, __builtin_fma(-kC1_6, b, kC5_6 * c));
     const double f2 = __builtin_fma(-kC1_6, e, __builtin_fma(kC1_3, c, kC5_6 * d));
-    const double* w = omega_lds + 3 * mask;
-    return __builtin_fma(w[2], f2, __builtin_fma(w[0], f0, w[1] * f1));
+    return __builtin_fma(w2, f2, __builtin_fma(w0, f0, w1 * f1));
+}
+
+template <bool A5>
+__device__ __forceinline__ double teno5_rec_fast(const SchemeParams& S, const DecisionConsts& K,
+                                                 const double* __restrict__ omega_lds,
+                                                 double a, double b, double c, double d,
+                                                 double e, uint32_t* code) {
+    uint32_t cd = 7u << 5;
+    if (S.scheme != 2) {
+        const Teno5Beta B = teno5_beta4(a, b, c, d, e);
+        if (!teno5_smooth(K.smooth_t, K.smooth_te, B)) cd = teno5_decide<A5>(S, K, B.b0, B.b1, B.b2, a, b, c, d, e);
+    }
+    *code = cd;
+    const double* w = omega_lds + 3 * (cd >> 5);
+    return teno5_combine(w[0], w[1], w[2], a, b, c, d, e);
 }
 
 // Local component order of a sweep along DIR: rho, normal momentum, the

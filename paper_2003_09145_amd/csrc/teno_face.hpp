@@ -13,68 +13,86 @@
 
 namespace teno {
 
-// Stage cell `idx` of the stencil buffer from its conserved state q (natural
+// What the faces around a cell need of it, from its conserved state q (natural
 // component order, ghost flip already applied): primitives (u_k = m_k / rho,
 // p = (gamma - 1)(E - ke), H = (E + p) / rho), the flux along DIR (eq 4.7) and
 // its split f+- = (F +- alpha U) / 2 in local order.
-template <int ND, int DIR, bool MIRROR = false>
-__device__ __forceinline__ void stage_cell(const double* q, double alpha, double gm1,
-                                       double* __restrict__ ext, int cap, int idx) {
+template <int ND>
+struct CellStage {
+    double fp[ND + 2], fm[ND + 2];  // split fluxes, local order
+    double srho, u[ND], H;
+};
+
+template <int ND, int DIR>
+__device__ __forceinline__ CellStage<ND> stage_values(const double* q, double alpha, double gm1) {
     constexpr int NC = ND + 2;
     using LO = LocalOrder<ND, DIR>;
-    // primitives (natural order), as u_k = m_k / rho, p = (gamma-1)(E - ke)
-    const double rho = q[0];
-    double u[ND];
-    const double rrho = rcp_nr(rho);
-    // the velocity quotients and sqrt(rho) are independent: their fast
-    // phases run together and share one correction branch
-    double srho;
-    {
-        double r[ND];
-        bool ok[ND];
-        bool all = sqrt_fast(rho, &srho);
-        const bool sok = all;
+    CellStage<ND> C;
+    const double rho = q[0], E = q[NC - 1];
+    double y;
+    const bool rok = rcp_exact(rho, &y);
+    // every quotient takes the fast form or none does: dividends in quot's
+    // range (their sum bounds them from above; E + p is checked below)
+    double big = fabs(E);
+    bool ok = rok;
 #pragma unroll
-        for (int kk = 0; kk < ND; ++kk) {
-            ok[kk] = div_r_fast(q[1 + kk], rho, rrho, &u[kk], &r[kk]);
-            all = all && ok[kk];
-        }
-        if (!all) {
-            if (!sok) srho = cr_sqrt_exact(rho);
+    for (int kk = 0; kk < ND; ++kk) {
+        C.u[kk] = quot(q[1 + kk], rho, y);
+        ok = ok && quot_ok(q[1 + kk]);
+        big = big + fabs(q[1 + kk]);
+    }
+    ok = ok && big < 0x1p600;
+    const bool sok = sqrt_fast(rho, &C.srho);
+    if (!(ok && sok)) {
+        if (!sok) C.srho = cr_sqrt_exact(rho);
+        if (!ok) {
 #pragma unroll
-            for (int kk = 0; kk < ND; ++kk)
-                if (!ok[kk]) u[kk] = div_r_fix(q[1 + kk], rho, u[kk], r[kk]);
+            for (int kk = 0; kk < ND; ++kk) C.u[kk] = cr_div(q[1 + kk], rho);
         }
     }
-    double mu = q[1] * u[0];
+    double mu = q[1] * C.u[0];
 #pragma unroll
-    for (int kk = 1; kk < ND; ++kk) mu = mu + q[1 + kk] * u[kk];
+    for (int kk = 1; kk < ND; ++kk) mu = mu + q[1 + kk] * C.u[kk];
     const double ke = 0.5 * mu;
-    const double E = q[NC - 1];
     const double p = gm1 * (E - ke);
-    const double H = cr_div_r(E + p, rho, rrho);
+    const double Ep = E + p;
+    C.H = quot(Ep, rho, y);
+    if (!(rok && quot_ok(Ep) && fabs(Ep) < 0x1p600)) C.H = cr_div(Ep, rho);
     // flux along DIR (natural order)
     double Fl[NC];
     Fl[0] = q[1 + DIR];
 #pragma unroll
     for (int kk = 0; kk < ND; ++kk)
-        Fl[1 + kk] = (kk == DIR) ? q[1 + kk] * u[DIR] + p : q[1 + kk] * u[DIR];
-    Fl[NC - 1] = (E + p) * u[DIR];
+        Fl[1 + kk] = (kk == DIR) ? q[1 + kk] * C.u[DIR] + p : q[1 + kk] * C.u[DIR];
+    Fl[NC - 1] = Ep * C.u[DIR];
     // global Lax-Friedrichs split in local order
 #pragma unroll
     for (int qq = 0; qq < NC; ++qq) {
         const int g = LO::nat(qq);
-        ext[(size_t)qq * cap + idx] = 0.5 * __builtin_fma(alpha, q[g], Fl[g]);
+        C.fp[qq] = 0.5 * __builtin_fma(alpha, q[g], Fl[g]);
+        C.fm[qq] = 0.5 * __builtin_fma(-alpha, q[g], Fl[g]);
+    }
+    return C;
+}
+
+// Stage cell `idx` of the stencil buffer.
+template <int ND, int DIR, bool MIRROR = false>
+__device__ __forceinline__ void stage_cell(const double* q, double alpha, double gm1,
+                                       double* __restrict__ ext, int cap, int idx) {
+    constexpr int NC = ND + 2;
+    const CellStage<ND> C = stage_values<ND, DIR>(q, alpha, gm1);
+#pragma unroll
+    for (int qq = 0; qq < NC; ++qq) {
+        ext[(size_t)qq * cap + idx] = C.fp[qq];
         // MIRROR: the f- rows hold the cells in reverse (column cap - 1 -
         // idx), so that its mirrored stencil i+3 .. i-1 reads ascending
         // columns too
-        ext[(size_t)(NC + qq) * cap + (MIRROR ? cap - 1 - idx : idx)] =
-            0.5 * __builtin_fma(-alpha, q[g], Fl[g]);
+        ext[(size_t)(NC + qq) * cap + (MIRROR ? cap - 1 - idx : idx)] = C.fm[qq];
     }
-    ext[(size_t)(2 * NC) * cap + idx] = srho;
+    ext[(size_t)(2 * NC) * cap + idx] = C.srho;
 #pragma unroll
-    for (int kk = 0; kk < ND; ++kk) ext[(size_t)(2 * NC + 1 + kk) * cap + idx] = u[kk];
-    ext[(size_t)(2 * NC + 1 + ND) * cap + idx] = H;
+    for (int kk = 0; kk < ND; ++kk) ext[(size_t)(2 * NC + 1 + kk) * cap + idx] = C.u[kk];
+    ext[(size_t)(2 * NC + 1 + ND) * cap + idx] = C.H;
 }
 
 // Roe average of the face between stencil cells o + 2 (i) and o + 3 (i+1)
@@ -94,39 +112,37 @@ struct FaceRoe {
     double b1ut[ND > 1 ? ND - 1 : 1];
 };
 
+// Roe average of the cells i (rl = sqrt(rho), ul, hl = H) and i + 1 (rr, ur, hr).
 template <int ND, int DIR>
-__device__ __forceinline__ FaceRoe<ND> face_roe(const double* __restrict__ ext, int cap, int o,
-                                                double gm1) {
-    constexpr int NC = ND + 2;
+__device__ __forceinline__ FaceRoe<ND> roe_average(double rl, const double* ul, double hl,
+                                                   double rr, const double* ur, double hr,
+                                                   double gm1) {
     using LO = LocalOrder<ND, DIR>;
-    const double* sr = ext + (size_t)(2 * NC) * cap;
-    const double* uu = ext + (size_t)(2 * NC + 1) * cap;
-    const double* hh = ext + (size_t)(2 * NC + 1 + ND) * cap;
     FaceRoe<ND> R;
-    R.rl = sr[o + 2];
-    R.rr = sr[o + 3];
-    const double rsum = R.rl + R.rr;
-    R.wsum = cr_div_r(1.0, rsum, rcp_nr(rsum));
+    R.rl = rl;
+    R.rr = rr;
+    R.wsum = cr_rcp(rl + rr);
 #pragma unroll
-    for (int kk = 0; kk < ND; ++kk)
-        R.ub[kk] = (R.rl * uu[(size_t)kk * cap + o + 2] + R.rr * uu[(size_t)kk * cap + o + 3]) * R.wsum;
-    R.Hb = (R.rl * hh[o + 2] + R.rr * hh[o + 3]) * R.wsum;
+    for (int kk = 0; kk < ND; ++kk) R.ub[kk] = (rl * ul[kk] + rr * ur[kk]) * R.wsum;
+    R.Hb = (rl * hl + rr * hr) * R.wsum;
     R.q2 = R.ub[0] * R.ub[0];
 #pragma unroll
     for (int kk = 1; kk < ND; ++kk) R.q2 = R.q2 + R.ub[kk] * R.ub[kk];
     R.c2 = gm1 * (R.Hb - 0.5 * R.q2);
     {
         // c = sqrt(c2) and b1 = (gamma - 1) / c2 are independent: one
-        // correction branch for both
-        double r;
+        // correction branch for both (gamma - 1 > 0 is tested by the range of
+        // quot's dividends once, uniformly)
+        double y;
         const bool sok = sqrt_fast(R.c2, &R.cs);
-        const bool bok = div_r_fast(gm1, R.c2, rcp_nr(R.c2), &R.b1, &r);
+        const bool bok = rcp_exact(R.c2, &y) && in_mid_range(gm1);
+        R.b1 = quot(gm1, R.c2, y);
         if (!(sok && bok)) {
             if (!sok) R.cs = cr_sqrt_exact(R.c2);
-            if (!bok) R.b1 = div_r_fix(gm1, R.c2, R.b1, r);
+            if (!bok) R.b1 = cr_div(gm1, R.c2);
         }
     }
-    R.ci = cr_div_r(1.0, R.cs, rcp_nr(R.cs));
+    R.ci = cr_rcp(R.cs);
     R.b2 = (0.5 * R.q2) * R.b1;
     R.un = R.ub[DIR];
 #pragma unroll
@@ -138,6 +154,22 @@ __device__ __forceinline__ FaceRoe<ND> face_roe(const double* __restrict__ ext, 
 #pragma unroll
     for (int kk = 1; kk < ND; ++kk) R.b1ut[kk - 1] = R.b1 * R.ut[kk - 1];
     return R;
+}
+
+template <int ND, int DIR>
+__device__ __forceinline__ FaceRoe<ND> face_roe(const double* __restrict__ ext, int cap, int o,
+                                                double gm1) {
+    constexpr int NC = ND + 2;
+    const double* sr = ext + (size_t)(2 * NC) * cap;
+    const double* uu = ext + (size_t)(2 * NC + 1) * cap;
+    const double* hh = ext + (size_t)(2 * NC + 1 + ND) * cap;
+    double ul[ND], ur[ND];
+#pragma unroll
+    for (int kk = 0; kk < ND; ++kk) {
+        ul[kk] = uu[(size_t)kk * cap + o + 2];
+        ur[kk] = uu[(size_t)kk * cap + o + 3];
+    }
+    return roe_average<ND, DIR>(sr[o + 2], ul, hh[o + 2], sr[o + 3], ur, hh[o + 3], gm1);
 }
 
 // Row s of the left eigenvector matrix (local order): acoustic fields s = 0

@@ -91,6 +91,9 @@ inline DecisionConsts decision_consts(const teno_grid* g, bool need_m) {
     K.hi_fac = K.ct_hi * (1.0 + kDecisionMargin);
     K.lo_fac = K.ct_lo * (1.0 - kDecisionMargin);
     K.ymarg = kDecisionMargin * K.nthr_d;
+    if (K.literal || K.need_m) K.smooth_t = -1.0;
+    K.eps4 = 4.0 * g->eps;
+    K.smooth_te = K.smooth_t * K.eps4;
     return K;
 }
 

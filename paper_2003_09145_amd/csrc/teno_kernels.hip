@@ -58,7 +58,8 @@ struct SweepArgs {
     int32_t rk;             // 0: write RHS; 1..3: fused RK stage
     int32_t stage;          // RK stage of this sweep (digest key; with ctrl->nsteps)
     int32_t ext_cap;        // LDS ext cells per wave
-    double dx;
+    double dx, rdx;         // spacing along the axis and RN(1 / dx)
+    int32_t rdx_ok;         // 1: dx is in the range of the fast quotients
     SchemeParams sch;
     DecisionConsts dk;
     const teno_boundary* bnd;  // nullable: per-end boundaries and gravity
@@ -364,11 +365,10 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
     __syncthreads();
 
     if (upd) {
-        const double rdx = rcp_nr(Ai.dx);
         double diff[NC], dq[NC], r[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) diff[c] = fh_c[c * 64 + jj] - fh_c[c * 64 + jj - 1];
-        cr_div_r_n<NC>(diff, Ai.dx, rdx, dq);  // independent quotients, one correction branch
+        cr_div_n<NC>(diff, Ai.dx, Ai.rdx, Ai.rdx_ok != 0, dq);
 #pragma unroll
         for (int c = 0; c < NC; ++c) r[c] = r_in[c] - dq[c];
         if (Ai.add_source) {
@@ -427,15 +427,20 @@ __global__ __launch_bounds__(256) void k_alpha(const double* __restrict__ U, int
         for (int c = 0; c < NC; ++c) q[c] = __builtin_nontemporal_load(&U[c * ncell + i]);
         const double rho = q[0];
         double u[ND];
-        const double rrho = rcp_nr(rho);
+        double y, m[ND];
+        const bool rok = rcp_exact(rho, &y);
 #pragma unroll
-        for (int k = 0; k < ND; ++k) u[k] = cr_div_r(q[1 + k], rho, rrho);
+        for (int k = 0; k < ND; ++k) m[k] = q[1 + k];
+        cr_div_n<ND>(m, rho, y, rok, u);
         double mu = q[1] * u[0];
 #pragma unroll
         for (int k = 1; k < ND; ++k) mu = mu + q[1 + k] * u[k];
         const double ke = 0.5 * mu;
         const double p = gm1 * (q[NC - 1] - ke);
-        const double cs = cr_sqrt(cr_div_r(gamma * p, rho, rrho));
+        double c2[1];
+        const double gp[1] = {gamma * p};
+        cr_div_n<1>(gp, rho, y, rok, c2);
+        const double cs = cr_sqrt(c2[0]);
         if (!(rho > 0.0) || !(p > 0.0) || !isfinite(cs)) bad = true;
 #pragma unroll
         for (int k = 0; k < ND; ++k) {
@@ -611,7 +616,7 @@ __global__ void k_selftest_arith(const double* a, const double* b, double* q, do
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < n) {
         q[i] = cr_div(a[i], b[i]);
-        q2[i] = cr_div_r(a[i], b[i], rcp_nr(b[i]));
+        q2[i] = cr_div_p(a[i], b[i]);
         s[i] = cr_sqrt(a[i]);
         r[i] = rcp_nr(b[i]);
         if (qp != nullptr) qp[i] = a[i] / b[i];
@@ -712,6 +717,8 @@ static hipError_t launch_sweep(const teno_grid* g, int dir, SweepArgs A, hipStre
     A.n = n;
     A.bc = g->bc[dir];
     A.dx = g->dx[dir];
+    A.rdx = 1.0 / A.dx;
+    A.rdx_ok = (A.dx >= 0x1p-400 && A.dx < 0x1p400) ? 1 : 0;
     A.ncell = ncell_of(g);
     A.bnd = g->boundary_dev;
     if (A.bnd == nullptr) A.add_source = 0;
