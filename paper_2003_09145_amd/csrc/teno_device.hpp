@@ -196,9 +196,10 @@ __device__ __forceinline__ bool quot_ok(double a) { return !(fabs(a) < 0x1p-600)
 
 // q[i] = a[i] / b correctly rounded for N independent dividends, from y =
 // RN(1 / b) (yok: certified, see rcp_exact): one correction branch for all.
+// zero: y is 0 and so is every quotient.
 template <int N>
 __device__ __forceinline__ void cr_div_n(const double (&a)[N], double b, double y, bool yok,
-                                         double (&q)[N]) {
+                                         double (&q)[N], bool zero = false) {
     bool ok = yok;
     double big = 0.0;
 #pragma unroll
@@ -207,7 +208,7 @@ __device__ __forceinline__ void cr_div_n(const double (&a)[N], double b, double 
         ok = ok && quot_ok(a[i]);
         big = (i == 0) ? fabs(a[i]) : big + fabs(a[i]);
     }
-    if (!(ok && big < 0x1p600)) {
+    if (!((ok && big < 0x1p600) || zero)) {
 #pragma unroll
         for (int i = 0; i < N; ++i) q[i] = cr_div(a[i], b);
     }
@@ -291,10 +292,10 @@ constexpr double kDecisionMargin = 0x1p-40;
 // (f_{i-2} .. f_{i+2}): sensors eta_j at j = i-1, i, i+1 (eq 2.18, denominator
 // df_{j+1/2}^2 + df_{j-1/2}^2), eta_{i+1/2} = their minimum, m = 1 - min(1,
 // eta / C_r), g = (1 - m)^4 (1 + 4 m), beta = alpha_1 - alpha_2 (1 - g),
-// C_T = 10^-floor(beta).  Operation order of the oracle; *k = floor(beta).
+// C_T = 10^-floor(beta).  Operation order of the oracle; returns floor(beta).
 template <class SP>
-__device__ __forceinline__ double teno5a_cutoff(const SP& S, double a, double b,
-                                                double c, double d, double e, int* k) {
+__device__ __forceinline__ int teno5a_cutoff(const SP& S, double a, double b, double c, double d,
+                                             double e) {
     const double df0 = b - a, df1 = c - b, df2 = d - c, df3 = e - d;
     // 2 x and 4 x are exact, so the fused forms below round exactly as the
     // oracle's product-then-add
@@ -313,9 +314,7 @@ __device__ __forceinline__ double teno5a_cutoff(const SP& S, double a, double b,
     const double om2 = om * om;
     const double g = (om2 * om2) * __builtin_fma(4.0, mA, 1.0);
     const double bA = S.a1 - S.a2 * (1.0 - g);
-    const int kk = (bA >= 0.0) ? (int)floor(bA) : S.kA_nan;
-    *k = kk;
-    return kLadder[kk];
+    return (bA >= 0.0) ? (int)floor(bA) : S.kA_nan;
 }
 
 // A5: the launch runs TENO5-A (scheme 3); its cutoff code is compiled only
@@ -367,7 +366,8 @@ __device__ __forceinline__ uint32_t teno5_decide_literal(const SP& S, double a,
         }
         ct = kLadder[m];
     } else if (A5) {
-        ct = teno5a_cutoff(S, a, b, c, d, e, &m);
+        m = teno5a_cutoff(S, a, b, c, d, e);
+        ct = kLadder[m];
     } else {
         ct = S.ct_fixed;
     }
@@ -381,13 +381,18 @@ __device__ __forceinline__ uint32_t teno5_decide_literal(const SP& S, double a,
 // The cutoff flags and the ladder index are discrete functions of the
 // literal formula.  They are first evaluated with approximate reciprocals;
 // if any decision value lies within kDecisionMargin of its threshold (or is
-// not finite) the lane re-evaluates the literal formula, so the decisions
-// equal the literal ones exactly.  b4_k = 4 beta_k.  SP, KP: SchemeParams and
-// DecisionConsts, in any address space.
-template <bool A5, class SP, class KP>
-__device__ __forceinline__ uint32_t teno5_decide(const SP& S, const KP& K,
-                                                 double b40, double b41, double b42, double a,
-                                                 double b, double c, double d, double e) {
+// not finite) the lane re-evaluates the literal formula (*certain = false), so
+// the decisions equal the literal ones exactly.  b4_k = 4 beta_k; ladder(k) =
+// 10^-k.  settled: the caller ignores the result (a lane that only accompanies
+// its wave).  WAVE: called by all lanes of a wave, whose branches are then
+// taken for the wave as a whole, so that ladder() may exchange values between
+// lanes.
+template <bool A5, bool WAVE, class SP, class KP, class LAD>
+__device__ __forceinline__ uint32_t teno5_decide_fast(const SP& S, const KP& K, const LAD& ladder,
+                                                      double b40, double b41, double b42,
+                                                      bool settled, double a, double b, double c,
+                                                      double d, double e, bool* certain) {
+    auto some = [](bool x) { return WAVE ? __ballot(x) != 0 : x; };
     bool sure = K.literal == 0;
     uint32_t m = 0, mask = 7u;
     if (sure) {
@@ -412,17 +417,16 @@ __device__ __forceinline__ uint32_t teno5_decide(const SP& S, const KP& K,
         // evaluates its cutoff exactly and uses it for both bounds.
         double chi_hi = K.ct_hi, chi_lo = K.ct_lo;
         if (A5) {
-            int kA;
-            chi_hi = chi_lo = teno5a_cutoff(S, a, b, c, d, e, &kA);
-            m = (uint32_t)kA;
+            m = (uint32_t)teno5a_cutoff(S, a, b, c, d, e);
+            chi_hi = chi_lo = ladder((int)m);
         }
         const double hi = (A5 ? chi_hi * (1.0 + kDecisionMargin) : K.hi_fac) * sum;
         const double lo = (A5 ? chi_lo * (1.0 - kDecisionMargin) : K.lo_fac) * sum;
         const bool k0 = g0 >= hi, k1 = g1 >= hi, k2 = g2 >= hi;
         const bool c0 = g0 < lo, c1 = g1 < lo, c2 = g2 < lo;
-        sure = isfinite(sum) && (k0 || c0) && (k1 || c1) && (k2 || c2);
+        sure = settled || (isfinite(sum) && (k0 || c0) && (k1 || c1) && (k2 || c2));
         mask = (k0 ? 1u : 0u) | (k1 ? 2u : 0u) | (k2 ? 4u : 0u);
-        if (S.scheme == 0 && (K.need_m || !sure)) {
+        if (S.scheme == 0 && (K.need_m || some(!sure))) {
             // ladder index from approximate x and theta.  A NaN t_k makes
             // sum NaN, which already sends the lane to the literal
             // formula; the clamp keeps the table index in range for any x.
@@ -440,19 +444,37 @@ __device__ __forceinline__ uint32_t teno5_decide(const SP& S, const KP& K,
             } else if (x >= K.h_lo) {
                 msure = false;
             }
-            if (!sure) {
-                const double ct = kLadder[m];
+            if (some(!sure)) {
+                const double ct = ladder((int)m);
                 const double rs = rcp_nr(sum);
                 const double x0 = g0 * rs, x1 = g1 * rs, x2 = g2 * rs;
                 const double band = kDecisionMargin * ct;
-                sure = isfinite(sum) && fabs(x0 - ct) > band && fabs(x1 - ct) > band &&
-                       fabs(x2 - ct) > band;
-                mask = (x0 < ct ? 0u : 1u) | (x1 < ct ? 0u : 2u) | (x2 < ct ? 0u : 4u);
+                const uint32_t lm = (x0 < ct ? 0u : 1u) | (x1 < ct ? 0u : 2u) | (x2 < ct ? 0u : 4u);
+                const bool ls = isfinite(sum) && fabs(x0 - ct) > band && fabs(x1 - ct) > band &&
+                                fabs(x2 - ct) > band;
+                // (with a ladder index that nothing needs, a sure lane stays so)
+                if (!sure) {
+                    mask = lm;
+                    sure = ls && msure;
+                } else if (K.need_m) {
+                    sure = msure;
+                }
+            } else {
+                sure = sure && msure;
             }
-            sure = sure && msure;
         }
     }
-    if (sure) return m | (mask << 5);
+    *certain = sure;
+    return m | (mask << 5);
+}
+template <bool A5>
+__device__ __forceinline__ uint32_t teno5_decide(const SchemeParams& S, const DecisionConsts& K,
+                                                 double b40, double b41, double b42, double a,
+                                                 double b, double c, double d, double e) {
+    bool sure;
+    const uint32_t cd = teno5_decide_fast<A5, false>(S, K, [](int k) { return kLadder[k]; }, b40, b41,
+                                                     b42, false, a, b, c, d, e, &sure);
+    if (sure) return cd;
     return teno5_decide_literal<A5>(S, a, b, c, d, e);
 }
 
@@ -509,7 +531,8 @@ __device__ __forceinline__ double teno5_rec_fast(const SchemeParams& S, const De
     uint32_t cd = 7u << 5;
     if (S.scheme != 2) {
         const Teno5Beta B = teno5_beta4(a, b, c, d, e);
-        if (!teno5_smooth(K.smooth_t, K.smooth_te, B)) cd = teno5_decide<A5>(S, K, B.b0, B.b1, B.b2, a, b, c, d, e);
+        if (!teno5_smooth(K.smooth_t, K.smooth_te, B))
+            cd = teno5_decide<A5>(S, K, B.b0, B.b1, B.b2, a, b, c, d, e);
     }
     *code = cd;
     const double* w = omega_lds + 3 * (cd >> 5);

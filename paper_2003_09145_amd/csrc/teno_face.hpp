@@ -112,7 +112,28 @@ struct FaceRoe {
     double b1ut[ND > 1 ? ND - 1 : 1];
 };
 
-// Roe average of the cells i (rl = sqrt(rho), ul, hl = H) and i + 1 (rr, ur, hr).
+// The scalars of the left eigenvector rows from Hb, q2 / 2, c, un and ut.
+template <int ND>
+__device__ __forceinline__ void left_scalars(FaceRoe<ND>& R, double gm1) {
+    R.c2 = gm1 * (R.Hb - R.hq2);
+    // b1 = (gamma - 1) / c2 and 1 / c: one correction branch for both
+    double y;
+    const bool bok = rcp_exact(R.c2, &y) && in_mid_range(gm1);
+    R.b1 = quot(gm1, R.c2, y);
+    const bool cok = rcp_exact(R.cs, &R.ci);
+    if (!(bok && cok)) {
+        if (!bok) R.b1 = cr_div(gm1, R.c2);
+        if (!cok) R.ci = cr_div(1.0, R.cs);
+    }
+    R.b2 = R.hq2 * R.b1;
+    R.unci = R.un * R.ci;
+    R.b1un = R.b1 * R.un;
+#pragma unroll
+    for (int kk = 1; kk < ND; ++kk) R.b1ut[kk - 1] = R.b1 * R.ut[kk - 1];
+}
+
+// Roe average of the cells i (rl = sqrt(rho), ul, hl = H) and i + 1 (rr, ur, hr),
+// without the left eigenvector's scalars (left_scalars).
 template <int ND, int DIR>
 __device__ __forceinline__ FaceRoe<ND> roe_average(double rl, const double* ul, double hl,
                                                    double rr, const double* ur, double hr,
@@ -128,31 +149,13 @@ __device__ __forceinline__ FaceRoe<ND> roe_average(double rl, const double* ul, 
     R.q2 = R.ub[0] * R.ub[0];
 #pragma unroll
     for (int kk = 1; kk < ND; ++kk) R.q2 = R.q2 + R.ub[kk] * R.ub[kk];
-    R.c2 = gm1 * (R.Hb - 0.5 * R.q2);
-    {
-        // c = sqrt(c2) and b1 = (gamma - 1) / c2 are independent: one
-        // correction branch for both (gamma - 1 > 0 is tested by the range of
-        // quot's dividends once, uniformly)
-        double y;
-        const bool sok = sqrt_fast(R.c2, &R.cs);
-        const bool bok = rcp_exact(R.c2, &y) && in_mid_range(gm1);
-        R.b1 = quot(gm1, R.c2, y);
-        if (!(sok && bok)) {
-            if (!sok) R.cs = cr_sqrt_exact(R.c2);
-            if (!bok) R.b1 = cr_div(gm1, R.c2);
-        }
-    }
-    R.ci = cr_rcp(R.cs);
-    R.b2 = (0.5 * R.q2) * R.b1;
+    R.hq2 = 0.5 * R.q2;
+    R.c2 = gm1 * (R.Hb - R.hq2);
+    R.cs = cr_sqrt(R.c2);
     R.un = R.ub[DIR];
+    R.unc = R.un * R.cs;
 #pragma unroll
     for (int kk = 1; kk < ND; ++kk) R.ut[kk - 1] = R.ub[LO::tan_axis(kk)];
-    R.unci = R.un * R.ci;
-    R.b1un = R.b1 * R.un;
-    R.unc = R.un * R.cs;
-    R.hq2 = 0.5 * R.q2;
-#pragma unroll
-    for (int kk = 1; kk < ND; ++kk) R.b1ut[kk - 1] = R.b1 * R.ut[kk - 1];
     return R;
 }
 
@@ -169,7 +172,9 @@ __device__ __forceinline__ FaceRoe<ND> face_roe(const double* __restrict__ ext, 
         ul[kk] = uu[(size_t)kk * cap + o + 2];
         ur[kk] = uu[(size_t)kk * cap + o + 3];
     }
-    return roe_average<ND, DIR>(sr[o + 2], ul, hh[o + 2], sr[o + 3], ur, hh[o + 3], gm1);
+    FaceRoe<ND> R = roe_average<ND, DIR>(sr[o + 2], ul, hh[o + 2], sr[o + 3], ur, hh[o + 3], gm1);
+    left_scalars<ND>(R, gm1);
+    return R;
 }
 
 // Row s of the left eigenvector matrix (local order): acoustic fields s = 0
@@ -201,6 +206,37 @@ __device__ __forceinline__ void left_row(const FaceRoe<ND>& R, int s, double (&L
 #pragma unroll
         for (int qq = 0; qq < NC; ++qq) Lr[qq] = 0.0;
         Lr[0] = -uts;
+    }
+}
+
+// Fh += R[:, s] * fh in local order, as fused multiply-adds (unit entries:
+// plain adds; the first field's products are exact additions to zero).
+template <int ND>
+__device__ __forceinline__ void add_right(const FaceRoe<ND>& R, int s, double fh,
+                                          double (&Fh)[ND + 2]) {
+    constexpr int NC = ND + 2;
+    const bool acoustic = (s == 0 || s == NC - 1), entropy = (s == 1);
+    if (acoustic) {
+        const bool minus = (s == 0);
+        Fh[0] = Fh[0] + fh;
+        Fh[1] = __builtin_fma(minus ? (R.un - R.cs) : (R.un + R.cs), fh, Fh[1]);
+#pragma unroll
+        for (int kk = 1; kk < ND; ++kk) Fh[1 + kk] = __builtin_fma(R.ut[kk - 1], fh, Fh[1 + kk]);
+        Fh[NC - 1] = __builtin_fma(minus ? (R.Hb - R.unc) : (R.Hb + R.unc), fh, Fh[NC - 1]);
+    } else if (entropy) {
+        Fh[0] = Fh[0] + fh;
+        Fh[1] = __builtin_fma(R.un, fh, Fh[1]);
+#pragma unroll
+        for (int kk = 1; kk < ND; ++kk) Fh[1 + kk] = __builtin_fma(R.ut[kk - 1], fh, Fh[1 + kk]);
+        Fh[NC - 1] = __builtin_fma(R.hq2, fh, Fh[NC - 1]);
+    } else {
+#pragma unroll
+        for (int kk = 1; kk < ND; ++kk) {
+            if (s == 1 + kk) {
+                Fh[1 + kk] = Fh[1 + kk] + fh;
+                Fh[NC - 1] = __builtin_fma(R.ut[kk - 1], fh, Fh[NC - 1]);
+            }
+        }
     }
 }
 
@@ -271,8 +307,6 @@ __device__ __forceinline__ void face_flux(const double* __restrict__ ext, int ca
     // face flux.
 #pragma unroll
     for (int s = 0; s < NC; ++s) {
-        const bool acoustic = (s == 0 || s == NC - 1);
-        const bool entropy = (s == 1);
         double Lr[NC];
         left_row<ND>(R, s, Lr);
         double fh = 0.0;
@@ -285,31 +319,7 @@ __device__ __forceinline__ void face_flux(const double* __restrict__ ext, int ca
             if (masks != nullptr) *masks |= (code >> 5) << (3 * (2 * s + sg));
             fh = sg ? fh + r : r;
         }
-        // accumulate R[:, s] * fh in local order, as fused multiply-adds
-        // (unit entries: plain adds; the first field's products are exact
-        // additions to zero)
-        if (acoustic) {
-            const bool minus = (s == 0);
-            Fh[0] = Fh[0] + fh;
-            Fh[1] = __builtin_fma(minus ? (R.un - R.cs) : (R.un + R.cs), fh, Fh[1]);
-#pragma unroll
-            for (int kk = 1; kk < ND; ++kk) Fh[1 + kk] = __builtin_fma(R.ut[kk - 1], fh, Fh[1 + kk]);
-            Fh[NC - 1] = __builtin_fma(minus ? (R.Hb - R.unc) : (R.Hb + R.unc), fh, Fh[NC - 1]);
-        } else if (entropy) {
-            Fh[0] = Fh[0] + fh;
-            Fh[1] = __builtin_fma(R.un, fh, Fh[1]);
-#pragma unroll
-            for (int kk = 1; kk < ND; ++kk) Fh[1 + kk] = __builtin_fma(R.ut[kk - 1], fh, Fh[1 + kk]);
-            Fh[NC - 1] = __builtin_fma(R.hq2, fh, Fh[NC - 1]);
-        } else {
-#pragma unroll
-            for (int kk = 1; kk < ND; ++kk) {
-                if (s == 1 + kk) {
-                    Fh[1 + kk] = Fh[1 + kk] + fh;
-                    Fh[NC - 1] = __builtin_fma(R.ut[kk - 1], fh, Fh[NC - 1]);
-                }
-            }
-        }
+        add_right<ND>(R, s, fh, Fh);
     }
 #pragma unroll
     for (int qq = 0; qq < NC; ++qq) Fnat[LO::nat(qq)] = Fh[qq];
