@@ -23,6 +23,7 @@
 #include "teno_device.hpp"
 #include "teno_face.hpp"
 #include "teno_host.hpp"
+#include "teno_stage.hpp"
 #include "teno_sweep.hpp"
 
 namespace teno {
@@ -33,6 +34,7 @@ constexpr int kCellsPerChunk = 63;
 // blocks of the LF-speed reduction: each writes one partial (3 maxima and a
 // non-physical flag), reduced afterwards by a single block (no atomics)
 constexpr int kAlphaBlocks = 2048;
+constexpr int kFewPartials = 256;  // the same of a small grid (kFewCells)
 
 // 64-bit mixer (the splitmix64 finaliser) for the cutoff-mask digest.
 __device__ __forceinline__ unsigned long long mask_hash(unsigned long long z) {
@@ -40,6 +42,65 @@ __device__ __forceinline__ unsigned long long mask_hash(unsigned long long z) {
     z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
     z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
     return z ^ (z >> 31);
+}
+
+// The work of the first sweep of a stage (StageWork::begin): false when the
+// stage does not run; *alpha the speed along x, *dt the step (stage 0).  smem:
+// LDS that is free again on return.
+template <int ND, int W, class AP>
+__device__ __forceinline__ bool stage_begin(const AP& Ai, double* smem, double* alpha, double* dt) {
+    constexpr int NC = ND + 2;
+    double r[4] = {0.0, 0.0, 0.0, 0.0};
+    teno_ctrl was;  // read ahead of the speeds
+    if (Ai.work.begin == 1) was = *Ai.work.ctrl;
+    const double* given = Ai.work.begin == 2 ? Ai.work.alpha_in : nullptr;
+    if (given != nullptr) {
+        for (int k = 0; k < 3; ++k) r[k] = given[k];
+    } else if (Ai.work.npart != 0) {
+        reduce_partials<ND>(Ai.work.part, Ai.work.npart, r, smem);
+    } else {
+        double amax[ND];
+#pragma unroll
+        for (int k = 0; k < ND; ++k) amax[k] = 0.0;
+        bool bad = false;
+        const double gamma = Ai.sch.gamma;
+        // four cells' loads in flight (past the last cell: of that one)
+        constexpr int kAhead = 4;
+        const int last = (int)Ai.ncell - 1;
+#pragma unroll 1
+        for (int i = threadIdx.x; i <= last; i += 64 * W * kAhead) {
+            double q[kAhead][NC];
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) {
+                const int at = i + 64 * W * j < last ? i + 64 * W * j : last;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) q[j][c] = Ai.U[c * Ai.ncell + at];
+            }
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j)
+                if (i + 64 * W * j <= last) cell_speeds<ND>(q[j], gamma, gamma - 1.0, amax, bad);
+        }
+#pragma unroll
+        for (int k = 0; k < ND; ++k) r[k] = amax[k];
+        r[3] = bad ? 1.0 : 0.0;
+        block_max4<ND>(r, smem);
+    }
+    *alpha = r[0];
+    const bool write = blockIdx.x == 0 && threadIdx.x == 0;
+    if (Ai.work.begin == 1) {
+        if (write && Ai.stage == 0) *Ai.work.done = 0u;
+        if (!stage_decide(Ai.work.ctrl, was, r, Ai.stage, ND, Ai.dxa[0], Ai.dxa[1], Ai.dxa[2], write, dt))
+            return false;
+        if (was.replay) *alpha = Ai.alpha[0];
+    } else if (write) {
+        for (int k = 0; k < 3; ++k) {
+            if (ND > 1) Ai.work.alpha_used[k] = r[k];
+            if (Ai.work.alpha_out != nullptr) Ai.work.alpha_out[k] = r[k];
+        }
+        if (Ai.work.status != nullptr)
+            *Ai.work.status = r[3] > 0.0 ? TENO_ERR_NONPHYSICAL : TENO_OK;
+    }
+    return true;
 }
 
 // CAPC: the stencil-buffer stride when it is known at compile time (it is
@@ -53,13 +114,16 @@ constexpr int kCapBlockLong = 264;
 
 template <int ND, int DIR, int W, bool DIGEST, int CAPC, bool A5>
 __global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep(SweepArgs A) {
+__attribute__((amdgpu_waves_per_eu(ND > 1 && CAPC == kCapBlockLong ? 5 : 4))) void k_sweep(SweepArgs A) {
     constexpr int NC = ND + 2;
     constexpr int NV = 2 * NC + ND + 2;  // f+ (NC), f- (NC), sqrt(rho), u (ND), H
     using LO = LocalOrder<ND, DIR>;
+    // only the last axis carries the stage update and the gravity terms
+    constexpr bool LAST = DIR == ND - 1;
     extern __shared__ double smem[];
 
-    if (A.ctrl != nullptr) {
+    if (A.small) touch_args<SweepArgs>();
+    if (A.ctrl != nullptr && (DIR != 0 || A.work.begin == 0)) {
         if (!A.ctrl->active || A.ctrl->status != 0) return;  // uniform across the grid
     }
     // The arguments are read through a pointer to the argument segment, where
@@ -110,6 +174,12 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
     // y and z sweeps store the f- rows reversed (measured faster there, and
     // slower along x)
     constexpr bool MIRROR = DIR != 0;
+    double alpha_begin = 0.0, dt_begin = 0.0;
+    if (DIR == 0 && Ai.work.begin != 0) {
+        if (!stage_begin<ND, W>(Ai, smem, &alpha_begin, &dt_begin)) return;  // uniform across the grid
+        alpha_begin = uniform(alpha_begin);
+        if (ND == 1) dt_begin = uniform(dt_begin);
+    }
     double* omega = smem;  // 24 doubles: eq 2.15 weights per cutoff mask
     const int per_wave = XCOOP ? 64 * NC : ((cap * NV > 64 * NC) ? cap * NV : 64 * NC);
     double* ext = XCOOP ? smem + 24 : smem + 24 + (size_t)wave * per_wave;
@@ -118,7 +188,9 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
     // face-flux write (XCOOP: the buffer is shared, and a block barrier
     // separates every wave's stencil reads from the flux writes).
     double* fhs = XCOOP ? smem + 24 + (size_t)wave * per_wave : ext;
-    if (threadIdx.x < 24) omega[threadIdx.x] = kOmega[threadIdx.x / 3][threadIdx.x % 3];
+    // (the table's load is in flight with the first cells')
+    const int to = threadIdx.x < 24 ? (int)threadIdx.x : 0;
+    const double omega_t = kOmega[to / 3][to % 3];
 
     const int64_t F0 = k * kCellsPerChunk;
     const int64_t F = F0 + lane;
@@ -144,7 +216,7 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
     const int count = (XCOOP || wave_ok) ? (int)(e_hi - e_lo) : 0;
 
     // ---- stage per-cell quantities of the ext cells [e_lo, e_hi) ----------
-    const double alpha = Ai.alpha[DIR];
+    const double alpha = DIR == 0 && Ai.work.begin != 0 ? alpha_begin : Ai.alpha[DIR];
     const double gm1 = sch_i.gamma - 1.0;
     const int64_t be0 = Ai.div32 ? (int64_t)div_by((int)e_lo, Ai.m6, Ai.s6)
                                 : e_lo / np6;       // line of the first ext cell (uniform)
@@ -197,6 +269,7 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
         stage_cell<ND, DIR, MIRROR>(q, alpha, gm1, ext_c, cap, cur);
     }
     }
+    if (threadIdx.x < 24) omega[threadIdx.x] = omega_t;
     __syncthreads();
 
     // ---- the cell this thread updates ----------------------------------------
@@ -225,7 +298,7 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
     double u_in[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) u_in[c] = 0.0;
-    if (upd && Ai.rk != 0) {
+    if (LAST && upd && Ai.rk != 0) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) u_in[c] = Ai.U[(size_t)c * Ai.ncell + cell];
     }
@@ -288,11 +361,14 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
         for (int c = 0; c < NC; ++c) {
             const size_t at = (size_t)c * Ai.ncell + cell;
             if (Ai.Rin != nullptr) r_in[c] = Ai.Rin[at];
-            if (Ai.rk >= 2) u_n[c] = Ai.Un[at];
+            if (LAST && Ai.rk >= 2) u_n[c] = Ai.Un[at];
         }
     }
     __syncthreads();
 
+    double v[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) v[c] = 0.0;
     if (upd) {
         double diff[NC], dq[NC], r[NC];
 #pragma unroll
@@ -300,7 +376,7 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
         cr_div_n<NC>(diff, Ai.dx, Ai.rdx, Ai.rdx_ok != 0, dq);
 #pragma unroll
         for (int c = 0; c < NC; ++c) r[c] = r_in[c] - dq[c];
-        if (Ai.add_source) {
+        if (LAST && Ai.add_source) {
             // gravity: rho g_d on each momentum, m . g on the energy (after the
             // flux differences of every axis)
             const double* g = Ai.bnd->gravity;
@@ -312,125 +388,91 @@ __attribute__((amdgpu_waves_per_eu(CAPC == kCapBlockLong ? 5 : 4))) void k_sweep
             for (int d = 1; d < ND; ++d) sE = sE + Ai.U[(1 + d) * Ai.ncell + cell] * g[d];
             r[NC - 1] = r[NC - 1] + sE;
         }
-        if (Ai.rk == 0) {
+        if (!LAST || Ai.rk == 0) {
 #pragma unroll
             for (int c = 0; c < NC; ++c) Ai.Rout[c * Ai.ncell + cell] = r[c];
         } else {
-            const double h = *Ai.dtp;
+            const double h = ND == 1 && Ai.work.begin != 0 && Ai.stage == 0 ? dt_begin : *Ai.dtp;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const size_t at = (size_t)c * Ai.ncell + cell;
-                double v;
                 if (Ai.rk == 1) {
-                    v = u_in[c] + h * r[c];
+                    v[c] = u_in[c] + h * r[c];
                 } else if (Ai.rk == 2) {
-                    v = (0.75 * u_n[c] + 0.25 * u_in[c]) + 0.25 * (h * r[c]);
+                    v[c] = (0.75 * u_n[c] + 0.25 * u_in[c]) + 0.25 * (h * r[c]);
                 } else {
-                    v = ((1.0 / 3.0) * u_n[c] + (2.0 / 3.0) * u_in[c]) + (2.0 / 3.0) * (h * r[c]);
+                    v[c] = ((1.0 / 3.0) * u_n[c] + (2.0 / 3.0) * u_in[c]) + (2.0 / 3.0) * (h * r[c]);
                 }
-                Ai.Uout[at] = v;
+                Ai.Uout[at] = v[c];
             }
         }
+    }
+    if (LAST && Ai.work.speeds != nullptr) {
+        double amax[ND], v4[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < ND; ++k) amax[k] = 0.0;
+        bool bad = false;
+        if (upd) cell_speeds<ND>(v, sch_i.gamma, gm1, amax, bad);
+#pragma unroll
+        for (int k = 0; k < ND; ++k) v4[k] = amax[k];
+        v4[3] = bad ? 1.0 : 0.0;
+        wave_max4<ND>(v4);
+        // (a reduction over the block first, for a quarter of the atomics, took
+        // 2 us more of a 1024 x 256 sweep's 32); non-negative doubles order as
+        // their bits do
+        const int k = lane & 3;
+        const double m = k == 0 ? v4[0] : k == 1 ? v4[1] : k == 2 ? v4[2] : v4[3];
+        if (lane < 4 && m > 0.0)
+            atomicMax((unsigned long long*)Ai.work.speeds + 4 * (chunk & (kSpeedSlots - 1)) + k,
+                      (unsigned long long)__double_as_longlong(m));
+    }
+    if (LAST && Ai.work.end != 0) {
+        __syncthreads();  // the block has read what ends with the step
+        if (threadIdx.x == 0 && atomicAdd(Ai.work.done, 1u) == gridDim.x - 1) step_end(Ai.work.ctrl);
     }
 }
 
 // ---- global Lax-Friedrichs speeds: alpha_d = max (|u_d| + c) -------------
 // Pass 1 (k_alpha): every block reduces its cells and writes part[4 b + k]
-// (k < 3: the maxima, 0 for absent axes; k = 3: 1.0 if the block saw a cell
-// with rho <= 0, p <= 0 or a non-finite sound speed).  Pass 2
-// (reduce_partials, inside the consumer kernel): one 256-thread block.
+// (k < 3: the maxima, 0 for absent axes; k = 3: 1.0 if the block saw a
+// non-physical cell).  Pass 2 (reduce_partials, inside the consumer kernel).
+// zero: nullable, 2 x kSpeedSlots slots that the sweeps of this step fill.
 template <int ND>
 __global__ __launch_bounds__(256) void k_alpha(const double* __restrict__ U, int64_t ncell,
-                                               double gamma, double* __restrict__ part) {
+                                               double gamma, double* __restrict__ part,
+                                               double* __restrict__ zero) {
     constexpr int NC = ND + 2;
-    __shared__ double red[4][4];
+    __shared__ double red[16];
     double amax[ND];
 #pragma unroll
     for (int k = 0; k < ND; ++k) amax[k] = 0.0;
     bool bad = false;
     const double gm1 = gamma - 1.0;
+    if (zero != nullptr && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < 8 * kSpeedSlots; i += blockDim.x) zero[i] = 0.0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < ncell;
          i += (int64_t)gridDim.x * blockDim.x) {
         double q[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) q[c] = __builtin_nontemporal_load(&U[c * ncell + i]);
-        const double rho = q[0];
-        double u[ND];
-        double y, m[ND];
-        const bool rok = rcp_exact(rho, &y);
-#pragma unroll
-        for (int k = 0; k < ND; ++k) m[k] = q[1 + k];
-        cr_div_n<ND>(m, rho, y, rok, u);
-        double mu = q[1] * u[0];
-#pragma unroll
-        for (int k = 1; k < ND; ++k) mu = mu + q[1 + k] * u[k];
-        const double ke = 0.5 * mu;
-        const double p = gm1 * (q[NC - 1] - ke);
-        double c2[1];
-        const double gp[1] = {gamma * p};
-        cr_div_n<1>(gp, rho, y, rok, c2);
-        const double cs = cr_sqrt(c2[0]);
-        if (!(rho > 0.0) || !(p > 0.0) || !isfinite(cs)) bad = true;
-#pragma unroll
-        for (int k = 0; k < ND; ++k) {
-            const double s = fabs(u[k]) + cs;
-            if (s > amax[k]) amax[k] = s;
-        }
+        cell_speeds<ND>(q, gamma, gm1, amax, bad);
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     double v4[4] = {0.0, 0.0, 0.0, bad ? 1.0 : 0.0};
 #pragma unroll
     for (int k = 0; k < ND; ++k) v4[k] = amax[k];
+    wave_max4<ND>(v4);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (lane == 0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double v = v4[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double o = __shfl_xor(v, off, 64);
-            if (o > v) v = o;
-        }
-        if (lane == 0) red[wv][k] = v;
+        for (int k = 0; k < 4; ++k) red[4 * wv + k] = v4[k];
     }
     __syncthreads();
     if (threadIdx.x < 4) {
         const int k = threadIdx.x;
-        double v = red[0][k];
+        double v = red[k];
         for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
-            if (red[w][k] > v) v = red[w][k];
+            if (red[4 * w + k] > v) v = red[4 * w + k];
         part[4 * (int64_t)blockIdx.x + k] = v;
-    }
-}
-
-// Maximum of the nblk partials (call from every thread of a 256-thread
-// block); out[0..2] the speeds, out[3] > 0 if any cell was non-physical.
-__device__ void reduce_partials(const double* __restrict__ part, int nblk, double out[4]) {
-    __shared__ double red[4][4];
-    double v4[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nblk; b += blockDim.x) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const double x = part[4 * b + k];
-            if (x > v4[k]) v4[k] = x;
-        }
-    }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double v = v4[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double o = __shfl_xor(v, off, 64);
-            if (o > v) v = o;
-        }
-        if (lane == 0) red[wv][k] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double v = red[0][k];
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
-            if (red[w][k] > v) v = red[w][k];
-        out[k] = v;
     }
 }
 
@@ -439,70 +481,31 @@ __device__ void reduce_partials(const double* __restrict__ part, int nblk, doubl
 __global__ __launch_bounds__(256) void k_copy_alpha(const double* part, int nblk,
                                                     const double* alpha_in, double* alpha_used,
                                                     double* alpha_out, int32_t* status) {
+    __shared__ double red[16];
     double r[4] = {0.0, 0.0, 0.0, 0.0};
-    if (alpha_in == nullptr) reduce_partials(part, nblk, r);
+    if (alpha_in == nullptr) reduce_partials<3>(part, nblk, r, red);
     const int k = threadIdx.x;
     if (k < 3) {
-        const double a = alpha_in ? alpha_in[k] : r[k];
+        const double a = alpha_in ? alpha_in[k] : k == 0 ? r[0] : k == 1 ? r[1] : r[2];
         alpha_used[k] = a;
         if (alpha_out) alpha_out[k] = a;
     }
     if (k == 0 && status != nullptr) *status = (r[3] > 0.0) ? TENO_ERR_NONPHYSICAL : TENO_OK;
 }
 
-// Stage bookkeeping of teno_step (one 256-thread block): reduce the speeds
-// of the stage input, flag a non-physical input (sticky), and at stage 0
-// set dt from eq dt1 / dt2 (3D: the harmonic form) clipped to t_end.
+// Stage bookkeeping of teno_step (one 256-thread block): reduce the speeds of
+// the stage input and decide the stage.
 __global__ __launch_bounds__(256) void k_stage_begin(teno_ctrl* ctrl, const double* part,
                                                      int nblk, int stage, int ndim, double dx0,
                                                      double dx1, double dx2) {
-    double r[4];
-    reduce_partials(part, nblk, r);
-    if (threadIdx.x != 0) return;
-    const bool bad = r[3] > 0.0;
-    if (stage == 0) {
-        ctrl->active = 0;
-        if (ctrl->status != 0 || !(ctrl->t < ctrl->t_end)) return;
-        if (bad) {
-            ctrl->status = TENO_ERR_NONPHYSICAL;
-            return;
-        }
-        if (!ctrl->replay) {
-            const double* a = r;
-            double dt;
-            if (ndim == 1) {
-                dt = cr_div(ctrl->cfl * dx0, a[0]);
-            } else if (ndim == 2) {
-                const double dtx = cr_div(dx0, a[0]);
-                const double dty = cr_div(dx1, a[1]);
-                dt = cr_div(ctrl->cfl * (dtx * dty), dtx + dty);
-            } else {
-                dt = cr_div(ctrl->cfl, (cr_div(a[0], dx0) + cr_div(a[1], dx1)) + cr_div(a[2], dx2));
-            }
-            if (ctrl->t + dt > ctrl->t_end) dt = ctrl->t_end - ctrl->t;
-            ctrl->dt = dt;
-            for (int k = 0; k < 3; ++k) ctrl->alpha[0][k] = a[k];
-        }
-        ctrl->active = 1;
-    } else {
-        if (!ctrl->active) return;
-        if (bad) ctrl->status = TENO_ERR_NONPHYSICAL;
-        if (ctrl->status != 0) {
-            ctrl->active = 0;
-            return;
-        }
-        if (!ctrl->replay)
-            for (int k = 0; k < 3; ++k) ctrl->alpha[stage][k] = r[k];
-    }
+    __shared__ double red[16];
+    double r[4], dt;
+    reduce_partials<3>(part, nblk, r, red);
+    if (threadIdx.x == 0) (void)stage_decide(ctrl, *ctrl, r, stage, ndim, dx0, dx1, dx2, true, &dt);
 }
 
 __global__ void k_step_end(teno_ctrl* ctrl) {
-    if (threadIdx.x != 0) return;
-    if (ctrl->active && ctrl->status == 0) {
-        ctrl->t = ctrl->t + ctrl->dt;
-        ctrl->nsteps += 1;
-    }
-    ctrl->active = 0;
+    if (threadIdx.x == 0) step_end(ctrl);
 }
 
 __global__ void k_ctrl_init(teno_ctrl* ctrl, double t0, double t_end, double cfl) {
@@ -559,8 +562,10 @@ __global__ void k_selftest_arith(const double* a, const double* b, double* q, do
 struct Scratch {  // device area at the end of the workspace
     double part[4 * kAlphaBlocks];  // LF-speed partials of k_alpha
     double alpha_used[4];
-    int32_t pad[8];
+    uint32_t done;  // blocks of the last sweep of a step that have finished
+    int32_t pad[7];
 };
+static_assert(4 * kAlphaBlocks >= 4 * kFewPartials + 8 * kSpeedSlots, "partials and slots share `part`");
 
 static int64_t ncell_of(const teno_grid* g) { return (int64_t)g->n[0] * g->n[1] * g->n[2]; }
 
@@ -706,18 +711,39 @@ static hipError_t launch_sweep(const teno_grid* g, int dir, SweepArgs A, hipStre
     return hipErrorInvalidValue;
 }
 
+// Small grids (up to kFewCells cells): the sweeps do the work around a stage
+// themselves (StageWork), ndim launches a stage and one more a step instead of
+// ndim + 2 a stage and one: a dependent launch that does next to nothing costs
+// 4 to 5 us, the same work inside a sweep 2 to 4.  Steps before and after: 128 x
+// 512 cells 97.4 -> 79.9 us, 362^2 133 -> 115, 1024 x 256 115 -> 112, 724^2 232
+// -> 221; but 1024^2 359 -> 379 (every block reads the speeds that one block
+// reads else), which keeps its own launches.
+// The first sweep of up to kAllCells cells takes the speeds from the state, in
+// every block (a step of 1024 cells 43 us, of 2048 46); of more, from k_alpha's
+// at most kFewPartials partials or from the slots that the sweep before it
+// filled (4096 and 8192 cells 46 us).
+constexpr int64_t kAllCells = 2048;
+constexpr int64_t kFewCells = 1 << 19;
+
+static bool few_cells(const teno_grid* g) {
+    return ncell_of(g) <= kFewCells && !march_grid(g, g->ndim - 1);
+}
+static bool all_cells(const teno_grid* g) { return ncell_of(g) <= kAllCells; }
+
 static int alpha_blocks(const teno_grid* g) {
     const int64_t b = (ncell_of(g) + 255) / 256;
-    return (int)(b < kAlphaBlocks ? b : kAlphaBlocks);
+    const int most = few_cells(g) ? kFewPartials : kAlphaBlocks;
+    return (int)(b < most ? b : most);
 }
 
-static hipError_t launch_alpha(const teno_grid* g, const double* U, double* part, hipStream_t st) {
+static hipError_t launch_alpha(const teno_grid* g, const double* U, double* part, double* zero,
+                               hipStream_t st) {
     const int64_t nc = ncell_of(g);
     const int blocks = alpha_blocks(g);
     switch (g->ndim) {
-        case 1: hipLaunchKernelGGL(k_alpha<1>, dim3(blocks), dim3(256), 0, st, U, nc, g->gamma, part); break;
-        case 2: hipLaunchKernelGGL(k_alpha<2>, dim3(blocks), dim3(256), 0, st, U, nc, g->gamma, part); break;
-        case 3: hipLaunchKernelGGL(k_alpha<3>, dim3(blocks), dim3(256), 0, st, U, nc, g->gamma, part); break;
+        case 1: hipLaunchKernelGGL(k_alpha<1>, dim3(blocks), dim3(256), 0, st, U, nc, g->gamma, part, zero); break;
+        case 2: hipLaunchKernelGGL(k_alpha<2>, dim3(blocks), dim3(256), 0, st, U, nc, g->gamma, part, zero); break;
+        case 3: hipLaunchKernelGGL(k_alpha<3>, dim3(blocks), dim3(256), 0, st, U, nc, g->gamma, part, zero); break;
     }
     return hipGetLastError();
 }
@@ -726,11 +752,13 @@ static hipError_t launch_alpha(const teno_grid* g, const double* U, double* part
 static int rhs_with_scratch(const teno_grid* g, const double* U, double* dUdt,
                             const double* alpha_in, double* alpha_out, int32_t* status,
                             uint8_t* dump, Scratch* S, hipStream_t st) {
-    if (alpha_in == nullptr) {
-        if (launch_alpha(g, U, S->part, st) != hipSuccess) return TENO_ERR_DEVICE;
+    const bool few = few_cells(g), all = all_cells(g);
+    if (alpha_in == nullptr && !all) {
+        if (launch_alpha(g, U, S->part, nullptr, st) != hipSuccess) return TENO_ERR_DEVICE;
     }
-    hipLaunchKernelGGL(k_copy_alpha, dim3(1), dim3(256), 0, st, S->part, alpha_blocks(g), alpha_in,
-                       S->alpha_used, alpha_out, status);
+    if (!few)
+        hipLaunchKernelGGL(k_copy_alpha, dim3(1), dim3(256), 0, st, S->part, alpha_blocks(g), alpha_in,
+                           S->alpha_used, alpha_out, status);
     int64_t dump_off = 0;
     for (int d = 0; d < g->ndim; ++d) {
         SweepArgs A;
@@ -742,6 +770,16 @@ static int rhs_with_scratch(const teno_grid* g, const double* U, double* dUdt,
         A.dump = dump ? dump + dump_off : nullptr;
         A.rk = 0;
         A.add_source = (d == g->ndim - 1) ? 1 : 0;
+        A.small = few ? 1 : 0;
+        if (few && d == 0) {
+            A.work.begin = 2;
+            A.work.npart = all ? 0 : alpha_blocks(g);
+            A.work.part = S->part;
+            A.work.alpha_in = alpha_in;
+            A.work.alpha_used = S->alpha_used;
+            A.work.alpha_out = alpha_out;
+            A.work.status = status;
+        }
         if (launch_sweep(g, d, A, st) != hipSuccess) return TENO_ERR_DEVICE;
         dump_off += ncell_of(g) / g->n[d] * (int64_t)(g->n[d] + 1) * 2 * (g->ndim + 2);
     }
@@ -895,12 +933,18 @@ int teno_sweep(const teno_grid* g, int32_t axis, const double* U, const double* 
 
 }  // extern "C"
 
+// nsteps steps.  events (one step): recorded around every sweep, so its sweeps
+// are launches of their own.
 static int step_impl(const teno_grid* g, double* U, teno_ctrl* ctrl, void* ws, size_t ws_bytes,
-                     void* const* events, void* stream) {
+                     int nsteps, void* const* events, void* stream) {
     if (validate(g) != TENO_OK || U == nullptr || ctrl == nullptr || ws == nullptr ||
         ws_bytes < workspace_bytes_impl(g))
         return TENO_ERR_ARG;
     hipStream_t st = (hipStream_t)stream;
+    for (int k = 1; k < nsteps; ++k) {
+        const int rc = step_impl(g, U, ctrl, ws, ws_bytes, 1, events, stream);
+        if (rc != TENO_OK) return rc;
+    }
     const size_t sb = state_bytes(g);
     double* R = (double*)ws;
     double* U1 = (double*)((char*)ws + sb);
@@ -908,10 +952,16 @@ static int step_impl(const teno_grid* g, double* U, teno_ctrl* ctrl, void* ws, s
     Scratch* S = scratch_of(g, ws);
     const double* stage_in[3] = {U, U1, U2};
     double* stage_out[3] = {U1, U2, U};
+    const bool few = few_cells(g), all = all_cells(g);
+    double* slots = S->part + 4 * kFewPartials;  // of stages 1 and 2
     for (int s = 0; s < 3; ++s) {
-        if (launch_alpha(g, stage_in[s], S->part, st) != hipSuccess) return TENO_ERR_DEVICE;
-        hipLaunchKernelGGL(k_stage_begin, dim3(1), dim3(256), 0, st, ctrl, S->part, alpha_blocks(g),
-                           s, g->ndim, g->dx[0], g->dx[1], g->dx[2]);
+        if (few ? s == 0 && !all : true) {
+            if (launch_alpha(g, stage_in[s], S->part, few ? slots : nullptr, st) != hipSuccess)
+                return TENO_ERR_DEVICE;
+        }
+        if (!few)
+            hipLaunchKernelGGL(k_stage_begin, dim3(1), dim3(256), 0, st, ctrl, S->part,
+                               alpha_blocks(g), s, g->ndim, g->dx[0], g->dx[1], g->dx[2]);
         for (int d = 0; d < g->ndim; ++d) {
             SweepArgs A;
             memset(&A, 0, sizeof(A));
@@ -930,6 +980,20 @@ static int step_impl(const teno_grid* g, double* U, teno_ctrl* ctrl, void* ws, s
                 A.Uout = stage_out[s];
                 A.add_source = 1;
             }
+            A.small = few ? 1 : 0;
+            if (few) {
+                A.work.ctrl = ctrl;
+                A.work.done = &S->done;
+                if (d == 0) {
+                    A.work.begin = 1;
+                    A.work.npart = all ? 0 : s == 0 ? alpha_blocks(g) : kSpeedSlots;
+                    A.work.part = s == 0 ? S->part : slots + 4 * kSpeedSlots * (s - 1);
+                }
+                if (d == g->ndim - 1) {
+                    if (s < 2 && !all) A.work.speeds = slots + 4 * kSpeedSlots * s;
+                    A.work.end = s == 2 ? 1 : 0;
+                }
+            }
             void* ev0 = events ? events[2 * (g->ndim * s + d)] : nullptr;
             void* ev1 = events ? events[2 * (g->ndim * s + d) + 1] : nullptr;
             if (ev0 != nullptr && hipEventRecord((hipEvent_t)ev0, st) != hipSuccess)
@@ -939,7 +1003,7 @@ static int step_impl(const teno_grid* g, double* U, teno_ctrl* ctrl, void* ws, s
                 return TENO_ERR_DEVICE;
         }
     }
-    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, st, ctrl);
+    if (!few) hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, st, ctrl);
     return hipGetLastError() == hipSuccess ? TENO_OK : TENO_ERR_DEVICE;
 }
 
@@ -947,12 +1011,12 @@ extern "C" {
 
 int teno_step(const teno_grid* g, double* U, teno_ctrl* ctrl, void* ws, size_t ws_bytes,
               void* stream) {
-    return step_impl(g, U, ctrl, ws, ws_bytes, nullptr, stream);
+    return step_impl(g, U, ctrl, ws, ws_bytes, 1, nullptr, stream);
 }
 
 int teno_step_timed(const teno_grid* g, double* U, teno_ctrl* ctrl, void* ws, size_t ws_bytes,
                     void* const* events, void* stream) {
-    return step_impl(g, U, ctrl, ws, ws_bytes, events, stream);
+    return step_impl(g, U, ctrl, ws, ws_bytes, 1, events, stream);
 }
 
 }  // extern "C"
@@ -1008,9 +1072,7 @@ int teno_runner_create(const teno_grid* g, double* U, teno_ctrl* ctrl, void* ws,
         teno_runner_destroy(r);
         return TENO_ERR_DEVICE;
     }
-    int rc = TENO_OK;
-    for (int32_t k = 0; k < steps_per_graph && rc == TENO_OK; ++k)
-        rc = step_impl(&r->g, U, ctrl, ws, ws_bytes, nullptr, r->cap);
+    const int rc = step_impl(&r->g, U, ctrl, ws, ws_bytes, steps_per_graph, nullptr, r->cap);
     const hipError_t e = hipStreamEndCapture(r->cap, &r->graph);
     if (rc != TENO_OK || e != hipSuccess ||
         hipGraphInstantiate(&r->exec, r->graph, nullptr, nullptr, 0) != hipSuccess) {
@@ -1027,11 +1089,8 @@ int teno_runner_run(teno_runner* r, int64_t nsteps, void* stream) {
     int64_t done = 0;
     for (; done + r->steps_per_graph <= nsteps; done += r->steps_per_graph)
         if (hipGraphLaunch(r->exec, st) != hipSuccess) return TENO_ERR_DEVICE;
-    for (; done < nsteps; ++done) {
-        const int rc = step_impl(&r->g, r->U, r->ctrl, r->ws, r->ws_bytes, nullptr, st);
-        if (rc != TENO_OK) return rc;
-    }
-    return TENO_OK;
+    if (done == nsteps) return TENO_OK;
+    return step_impl(&r->g, r->U, r->ctrl, r->ws, r->ws_bytes, (int)(nsteps - done), nullptr, st);
 }
 
 }  // extern "C"

@@ -43,14 +43,6 @@ using ArgsPtr = KernArgs<MarchArgs>;
 using ArgsPtr = const MarchArgs*;
 #endif
 
-// A value that is the same in every lane, in scalar registers.
-__device__ __forceinline__ double uniform(double x) {
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
-}
-
 // Element at a uniform address plus a lane's byte offset.  The empty asm keeps
 // the uniform part in scalar registers (the optimizer would otherwise add the
 // lane's offset to a row first and form 64-bit vector addresses from it).
@@ -515,13 +507,17 @@ static int64_t march_cols(const teno_grid* g, int dir) {
 // 0.97 of the speed at 2048^2 (two of three seeds; 1.00 the third) and 1.03
 // and 0.96 at 256^3 (two seeds), 0.92 to 0.97 at 200 x 180 x 190, which is
 // left to the face stream; smooth 256^3 takes 1.15, 2048^2 1.09.
-bool march_takes(const teno_grid* g, int dir, const SweepArgs& A, bool digest) {
-    if (dir == 0 || digest || A.dump != nullptr || A.Rin == nullptr) return false;
+bool march_grid(const teno_grid* g, int dir) {
+    if (dir == 0) return false;
     const int64_t rows = (march_cols(g, dir) + 63) / 64 * g->n[dir];
     if (rows < (g->ndim == 2 ? 60000 : 160000) || g->n[dir] < 24) return false;
     // 32-bit lane offsets within a wave's columns and block count
     const int64_t plane = (int64_t)g->n[0] * g->n[1];
     return (63 / g->n[0] + 2) * plane < (int64_t(1) << 29) && rows < (int64_t(1) << 31);
+}
+
+bool march_takes(const teno_grid* g, int dir, const SweepArgs& A, bool digest) {
+    return !digest && A.dump == nullptr && A.Rin != nullptr && march_grid(g, dir);
 }
 
 hipError_t launch_march(const teno_grid* g, int dir, const SweepArgs& A0, hipStream_t st) {

@@ -10,6 +10,30 @@
 
 namespace teno {
 
+// Work around an RK stage (or a right-hand side) that a small grid's sweeps do
+// themselves instead of kernels of their own (step_impl, rhs_with_scratch).
+struct StageWork {
+    // first axis: every block takes the LF speeds from `npart` partials at
+    // `part` (npart = 0: from all cells of U) and decides what the stage does;
+    // the first block records it
+    int32_t begin;           // 0: none; 1: a stage of teno_step; 2: a right-hand side
+    int32_t npart;
+    const double* part;
+    teno_ctrl* ctrl;         // begin = 1
+    const double* alpha_in;  // begin = 2: nullable, frozen speeds
+    double* alpha_used;
+    double* alpha_out;       // nullable
+    int32_t* status;         // nullable
+    // last axis of stages 1 and 2: the speeds of the stage output, as maxima
+    // over kSpeedSlots slots of 4 doubles that were zeroed before
+    double* speeds;          // nullable
+    // last sweep of a step: blocks that are done, zeroed by the first sweep;
+    // the last one ends the step
+    uint32_t* done;          // nullable
+    int32_t end;
+};
+constexpr int kSpeedSlots = 64;
+
 // Per-launch description of one sweep.
 struct SweepArgs {
     const double* U;        // state the stencils read (stage input)
@@ -22,6 +46,7 @@ struct SweepArgs {
     const double* dtp;      // dt of the fused RK stage (rk > 0)
     unsigned long long* digest;  // nullable: cutoff-mask digest accumulator
     int32_t axis;
+    int32_t small;          // 1: a small grid, whose blocks read the arguments ahead (touch_args)
     uint8_t* dump;          // nullable: decision bytes of this axis
     int64_t ncell;
     int64_t line_step;      // cell-index step between consecutive lines of a column
@@ -47,6 +72,7 @@ struct SweepArgs {
     // div32: every face and ext index of a column is below 2^31
     uint32_t m1, s1, m6, s6, mc, sc;
     int32_t div32;
+    StageWork work;
 };
 
 // Boundary kind of the ghost cells at end `end` of axis `dir` for the line
@@ -78,11 +104,37 @@ __device__ __forceinline__ int boundary_kind(const teno_boundary* bnd, const ten
     return kind;
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ double uniform(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
 // A pointer to a kernel's argument segment (constant address space).
 template <class T>
 using KernArgs = __attribute__((address_space(4))) const T*;
 
-// The marching sweep (teno_march.hip): true when it takes this launch.
+// Reads one word of every cache line of the kernel's arguments at entry.  Scalar
+// loads of the arguments are issued where their values are used; on a small grid
+// each first touch of a line is then a full memory latency in a serial chain.
+// Without and with it: a step of 128 x 512 cells 87 / 84 us, of 2048 48 / 47,
+// a right-hand side of 200 11.3 / 10.9; but of 2048^2 1159 / 1167.
+template <class T>
+__device__ __forceinline__ void touch_args() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto p = (KernArgs<uint32_t>)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t x = 0;
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); k += 16) x |= p[k];
+    __asm__ __volatile__("" ::"s"(x));
+#endif
+}
+
+// The marching sweep (teno_march.hip): true when it takes a grid's sweeps along
+// an axis (but for those with decision bytes or digests); when it takes this launch.
+bool march_grid(const teno_grid* g, int dir);
 bool march_takes(const teno_grid* g, int dir, const SweepArgs& A, bool digest);
 hipError_t launch_march(const teno_grid* g, int dir, const SweepArgs& A, hipStream_t st);
 
