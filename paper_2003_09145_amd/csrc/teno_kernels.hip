@@ -941,6 +941,8 @@ static int step_impl(const teno_grid* g, double* U, teno_ctrl* ctrl, void* ws, s
         ws_bytes < workspace_bytes_impl(g))
         return TENO_ERR_ARG;
     hipStream_t st = (hipStream_t)stream;
+    if (events == nullptr && line_takes(g))
+        return launch_line(g, U, ctrl, nsteps, st) == hipSuccess ? TENO_OK : TENO_ERR_DEVICE;
     for (int k = 1; k < nsteps; ++k) {
         const int rc = step_impl(g, U, ctrl, ws, ws_bytes, 1, events, stream);
         if (rc != TENO_OK) return rc;

@@ -138,4 +138,8 @@ bool march_grid(const teno_grid* g, int dir);
 bool march_takes(const teno_grid* g, int dir, const SweepArgs& A, bool digest);
 hipError_t launch_march(const teno_grid* g, int dir, const SweepArgs& A, hipStream_t st);
 
+// Whole steps of a short 1D line in one launch (teno_line.hip).
+bool line_takes(const teno_grid* g);
+hipError_t launch_line(const teno_grid* g, double* U, teno_ctrl* ctrl, int nsteps, hipStream_t st);
+
 }  // namespace teno

@@ -1,4 +1,5 @@
-"""Steps of small grids, whose sweeps do the work around a stage themselves, bit for bit
+"""Steps of small grids, where one block takes whole steps of a 1D line and the
+sweeps of other small grids do the work around a stage themselves, bit for bit
 against the oracle: sizes on both sides of every line of the dispatch, the
 clipped last step, runs recorded with a remainder, and the same steps with the
 sweeps as launches of their own."""
