@@ -100,7 +100,11 @@ inline DecisionConsts decision_consts(const teno_grid* g, bool need_m) {
 inline DecisionConsts decision_consts_base(const teno_grid* g, bool need_m) {
     DecisionConsts K;
     memset(&K, 0, sizeof(K));
-    K.literal = (g->flags & TENO_FLAG_LITERAL_DECISIONS) ? 1 : 0;
+    // With an epsilon near the ends of the double range the indicators that
+    // matter are subnormal or overflow, and four times an indicator does not
+    // round as the indicator does (at 2^-1074 a mask in 100000 differed).
+    const bool plain_eps = g->eps >= 0x1p-900 && g->eps <= 0x1p900;
+    K.literal = (g->flags & TENO_FLAG_LITERAL_DECISIONS) || !plain_eps ? 1 : 0;
     K.need_m = need_m ? 1 : 0;
     K.smooth_t = -1.0;
     K.h_hi = K.h_lo = NAN;
