@@ -196,10 +196,9 @@ __device__ __forceinline__ bool quot_ok(double a) { return !(fabs(a) < 0x1p-600)
 
 // q[i] = a[i] / b correctly rounded for N independent dividends, from y =
 // RN(1 / b) (yok: certified, see rcp_exact): one correction branch for all.
-// zero: y is 0 and so is every quotient.
 template <int N>
 __device__ __forceinline__ void cr_div_n(const double (&a)[N], double b, double y, bool yok,
-                                         double (&q)[N], bool zero = false) {
+                                         double (&q)[N]) {
     bool ok = yok;
     double big = 0.0;
 #pragma unroll
@@ -208,7 +207,7 @@ __device__ __forceinline__ void cr_div_n(const double (&a)[N], double b, double 
         ok = ok && quot_ok(a[i]);
         big = (i == 0) ? fabs(a[i]) : big + fabs(a[i]);
     }
-    if (!((ok && big < 0x1p600) || zero)) {
+    if (!(ok && big < 0x1p600)) {
 #pragma unroll
         for (int i = 0; i < N; ++i) q[i] = cr_div(a[i], b);
     }

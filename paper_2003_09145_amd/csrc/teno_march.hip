@@ -329,15 +329,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma unroll
         for (int j = 0; j < 5; ++j) fmp[j] = &fmr[s5 - j < 0 ? s5 - j + 5 : s5 - j][0][lane];
         next_slot();
-        // The first face finishes no cell: it stores row j0 unchanged (weights 1
-        // and 0, every other term made -0), so that no store is behind a branch
-        // -- loads and stores share one in-order counter, and a path that may
-        // have skipped the stores makes the wait for the next row wait for them
-        // too.  (The output may be the buffer of U^n or of the partial
-        // right-hand side, whose row j0 the next face reads again.)
-        const double c0 = it == 0 ? 1.0 : w0, c1 = it == 0 ? 0.0 : w1;
-        const double rdx = it == 0 ? 0.0 : Ai.s.rdx;
-        const long long first_neg = it == 0 ? (long long)0x8000000000000000ull : 0ll;
+        // The first face finishes no cell: it stores row j0 unchanged (by selects:
+        // a flux or a stage input that is not finite changes nothing either), so
+        // that no store is behind a branch -- loads and stores share one in-order
+        // counter, and a path that may have skipped the stores makes the wait for
+        // the next row wait for them too.  (The output may be the buffer of U^n or
+        // of the partial right-hand side, whose row j0 the next face reads again;
+        // a first stage's output is neither and takes any value.)
+        const bool none = it == 0;
         double r_in[NC], base[NC], u_n[NC];
         const int64_t row = cb0 + (int64_t)(j0 + (it > 0 ? it - 1 : 0)) * stride;
         double fh[NC];        // reconstructed characteristic fluxes
@@ -371,7 +370,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                     if (MODE == 2) {
 #pragma unroll
                         for (int k = 0; k < NC; ++k)
-                            base[k] = c0 * u_n[k] + __longlong_as_double(__double_as_longlong(c1 * base[k]) | first_neg);
+                            base[k] = none ? u_n[k] : w0 * u_n[k] + w1 * base[k];
                     }
                     const int jn = j0 + it + 3;
                     load_row(jn < n + 2 ? jn : n + 2, qn, &neg);
@@ -460,13 +459,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         double diff[NC], dq[NC], ro[NC];
 #pragma unroll
         for (int k = 0; k < NC; ++k) diff[LO::nat(k)] = Fh[k] - Fprev[k];
-        cr_div_n<NC>(diff, Ai.s.dx, rdx, Ai.s.rdx_ok != 0, dq, it == 0);
+        cr_div_n<NC>(diff, Ai.s.dx, Ai.s.rdx, Ai.s.rdx_ok != 0, dq);
 #pragma unroll
-        for (int k = 0; k < NC; ++k) {
-            if (MODE == 0)  // +0, never -0, at the first face
-                dq[k] = __longlong_as_double(__double_as_longlong(dq[k]) & ~first_neg);
-            ro[k] = r_in[k] - dq[k];
-        }
+        for (int k = 0; k < NC; ++k) ro[k] = MODE == 0 && none ? r_in[k] : r_in[k] - dq[k];
         if (Ai.s.add_source && it > 0) {
             const double* g = Ai.s.bnd->gravity;
             const double rho = ld(pU + row, lo8);
@@ -483,8 +478,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
             if (MODE == 1) ro[k] = base[k] + h * ro[k];
-            if (MODE == 2)
-                ro[k] = base[k] + __longlong_as_double(__double_as_longlong(c1 * (h * ro[k])) | first_neg);
+            if (MODE == 2) ro[k] = none ? base[k] : base[k] + w1 * (h * ro[k]);
             st(pO + k * ncell + row, lo8, ro[k]);
         }
 #pragma unroll
