@@ -137,5 +137,36 @@ inline DecisionConsts decision_consts_base(const teno_grid* g, bool need_m) {
     return K;
 }
 
+// Columns of the marching sweep along `dir` (y or z).
+inline int64_t march_cols(const teno_grid* g, int dir) {
+    return dir == 1 ? (int64_t)g->n[0] * g->n[2] : (int64_t)g->n[0] * g->n[1];
+}
+
+// Whether the marching sweep (teno_march.hip) takes a grid's sweeps along `dir`,
+// but for those with decision bytes or digests.  It pays once its waves (64
+// columns each) have enough rows to fill the chip at two waves per SIMD; below
+// that the face-stream sweep spreads the same faces over more waves.  Smooth
+// flow, march against face stream along y, us: 2D 1024^2 54 / 51, 1531 x 977 65 /
+// 71, 2048 x 1024 79 / 93, 2048^2 143 / 186; 3D 128^3 148 / 114, 160^3 236 / 219,
+// 192^3 340 / 366, 256^3 685 / 842.
+// A cut stencil costs the march more (a decision pass stops all 64 columns), so
+// the line lies above the crossing: steps with three oblique jumps and broken-up
+// post-shock noise take 0.97 of the speed at 2048^2 (two of three seeds; 1.00 the
+// third) and 1.03 and 0.96 at 256^3 (two seeds), 0.92 to 0.97 at 200 x 180 x 190,
+// which is left to the face stream; smooth 256^3 takes 1.15, 2048^2 1.09.
+// Idle lanes cost their share, which the face-stream sweep does not pay: a sweep
+// of 3 x 60005 cells took 138 us against 13, 33 x 60011 153 / 99, 96 x 100000 481 /
+// 421, 200 x 64000 587 / 554, but 128 x 100000 477 / 557; so at most a lane in 16
+// may be idle.
+inline bool march_grid(const teno_grid* g, int dir) {
+    if (dir == 0) return false;
+    const int64_t cols = march_cols(g, dir), groups = (cols + 63) / 64;
+    const int64_t rows = groups * g->n[dir];
+    if (rows < (g->ndim == 2 ? 60000 : 160000) || g->n[dir] < 24) return false;
+    if (16 * cols < 15 * 64 * groups) return false;
+    // 32-bit lane offsets within a wave's columns and block count
+    const int64_t plane = (int64_t)g->n[0] * g->n[1];
+    return (63 / g->n[0] + 2) * plane < (int64_t(1) << 29) && rows < (int64_t(1) << 31);
+}
 
 }  // namespace teno

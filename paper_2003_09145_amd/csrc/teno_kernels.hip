@@ -725,9 +725,8 @@ static hipError_t launch_sweep(const teno_grid* g, int dir, SweepArgs A, hipStre
 constexpr int64_t kAllCells = 2048;
 constexpr int64_t kFewCells = 1 << 19;
 
-static bool few_cells(const teno_grid* g) {
-    return ncell_of(g) <= kFewCells && !march_grid(g, g->ndim - 1);
-}
+// (The march, whose sweeps do none of this, takes no grid of less than 3.6 million.)
+static bool few_cells(const teno_grid* g) { return ncell_of(g) <= kFewCells; }
 static bool all_cells(const teno_grid* g) { return ncell_of(g) <= kAllCells; }
 
 static int alpha_blocks(const teno_grid* g) {

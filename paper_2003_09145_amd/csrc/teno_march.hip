@@ -486,30 +486,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
 }
 
-static int64_t march_cols(const teno_grid* g, int dir) {
-    return dir == 1 ? (int64_t)g->n[0] * g->n[2] : (int64_t)g->n[0] * g->n[1];
-}
-
-// The march pays once its waves (64 columns each) have enough rows to fill the
-// chip at two waves per SIMD; below that the face-stream sweep spreads the same
-// faces over more waves.  Smooth flow, march against face stream along y, us:
-// 2D 1024^2 54 / 51, 1531 x 977 65 / 71, 2048 x 1024 79 / 93, 2048^2 143 / 186;
-// 3D 128^3 148 / 114, 160^3 236 / 219, 192^3 340 / 366, 256^3 685 / 842.
-// A cut stencil costs the march more (a decision pass stops all 64 columns),
-// so the line lies above the crossing, where a flow full of jumps is about
-// even: steps with three oblique jumps and broken-up post-shock noise take
-// 0.97 of the speed at 2048^2 (two of three seeds; 1.00 the third) and 1.03
-// and 0.96 at 256^3 (two seeds), 0.92 to 0.97 at 200 x 180 x 190, which is
-// left to the face stream; smooth 256^3 takes 1.15, 2048^2 1.09.
-bool march_grid(const teno_grid* g, int dir) {
-    if (dir == 0) return false;
-    const int64_t rows = (march_cols(g, dir) + 63) / 64 * g->n[dir];
-    if (rows < (g->ndim == 2 ? 60000 : 160000) || g->n[dir] < 24) return false;
-    // 32-bit lane offsets within a wave's columns and block count
-    const int64_t plane = (int64_t)g->n[0] * g->n[1];
-    return (63 / g->n[0] + 2) * plane < (int64_t(1) << 29) && rows < (int64_t(1) << 31);
-}
-
 bool march_takes(const teno_grid* g, int dir, const SweepArgs& A, bool digest) {
     return !digest && A.dump == nullptr && A.Rin != nullptr && march_grid(g, dir);
 }

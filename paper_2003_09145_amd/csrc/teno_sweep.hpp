@@ -132,9 +132,7 @@ __device__ __forceinline__ void touch_args() {
 #endif
 }
 
-// The marching sweep (teno_march.hip): true when it takes a grid's sweeps along
-// an axis (but for those with decision bytes or digests); when it takes this launch.
-bool march_grid(const teno_grid* g, int dir);
+// The marching sweep (teno_march.hip): true when it takes this launch.
 bool march_takes(const teno_grid* g, int dir, const SweepArgs& A, bool digest);
 hipError_t launch_march(const teno_grid* g, int dir, const SweepArgs& A, hipStream_t st);
 
