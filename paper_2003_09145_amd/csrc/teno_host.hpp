@@ -142,31 +142,56 @@ inline int64_t march_cols(const teno_grid* g, int dir) {
     return dir == 1 ? (int64_t)g->n[0] * g->n[2] : (int64_t)g->n[0] * g->n[1];
 }
 
-// Whether the marching sweep (teno_march.hip) takes a grid's sweeps along `dir`,
-// but for those with decision bytes or digests.  It pays once its waves (64
-// columns each) have enough rows to fill the chip at two waves per SIMD; below
-// that the face-stream sweep spreads the same faces over more waves.  Smooth
-// flow, march against face stream along y, us: 2D 1024^2 54 / 51, 1531 x 977 65 /
-// 71, 2048 x 1024 79 / 93, 2048^2 143 / 186; 3D 128^3 148 / 114, 160^3 236 / 219,
-// 192^3 340 / 366, 256^3 685 / 842.
-// A cut stencil costs the march more (a decision pass stops all 64 columns), so
-// the line lies above the crossing: steps with three oblique jumps and broken-up
-// post-shock noise take 0.97 of the speed at 2048^2 (two of three seeds; 1.00 the
-// third) and 1.03 and 0.96 at 256^3 (two seeds), 0.92 to 0.97 at 200 x 180 x 190,
-// which is left to the face stream; smooth 256^3 takes 1.15, 2048^2 1.09.
+// Whether the marching sweep (teno_march.hip) takes a grid's sweeps along `dir`
+// (with or without the stage update), but for those with decision bytes or
+// digests.  It pays once its waves (64 columns each) have enough rows to fill the
+// chip at two waves per SIMD; below that the face-stream sweep spreads the same
+// faces over more waves.  A stencil that is not smooth costs the march more (a
+// decision pass stops all 64 columns), so the lines lie where flows full of jumps
+// (three planar ones, and the noise behind them) are about even.  Speed against
+// the face stream, jump flows (one seed each), then smooth flows:
+//  - 2D sweeps with the stage update, step of 2048^2 (65536 rows) 0.95, 1.00, 1.01,
+//    1.03, 1.03, and 1.05 to 1.07; of 1792 x 2048, below the line, 0.99 smooth; of
+//    2560^2 1.00, 1.01, 1.07, and 1.06;
+//  - without it, right-hand side of 2048^2 0.93, 0.96, 0.98, and 0.99; of 2560^2
+//    (102400 rows) 0.98, 1.03, and 1.03;
+//  - 3D, step of 220^3 (166540 rows) 0.97, 1.02, 1.04, and 1.06; of 256^3 1.00, 1.03,
+//    1.04, and 1.08; of 320^3 1.10 smooth.
 // Idle lanes cost their share, which the face-stream sweep does not pay: a sweep
 // of 3 x 60005 cells took 138 us against 13, 33 x 60011 153 / 99, 96 x 100000 481 /
 // 421, 200 x 64000 587 / 554, but 128 x 100000 477 / 557; so at most a lane in 16
 // may be idle.
-inline bool march_grid(const teno_grid* g, int dir) {
+inline bool march_grid(const teno_grid* g, int dir, bool stage) {
     if (dir == 0) return false;
     const int64_t cols = march_cols(g, dir), groups = (cols + 63) / 64;
     const int64_t rows = groups * g->n[dir];
-    if (rows < (g->ndim == 2 ? 60000 : 160000) || g->n[dir] < 24) return false;
+    const int64_t least = g->ndim == 3 ? 160000 : stage ? 60000 : 100000;
+    if (rows < least || g->n[dir] < 24) return false;
     if (16 * cols < 15 * 64 * groups) return false;
     // 32-bit lane offsets within a wave's columns and block count
     const int64_t plane = (int64_t)g->n[0] * g->n[1];
     return (63 / g->n[0] + 2) * plane < (int64_t(1) << 29) && rows < (int64_t(1) << 31);
+}
+
+// Segments of the `n` rows of each of `groups` groups of columns: at least 8 rows
+// each, in more than two rounds of the 2048 waves the chip holds, the number whose
+// rounds take the fewest rows, with 1.5 rows for the staging ahead of a segment.
+// Two rounds are 1 to 2% faster on a smooth flow, but then a wave on a jump ends
+// long after the others: steps of 256^3 with three jumps took 10.7, 9.1 and 8.7 ms
+// (three seeds) in two rounds, 9.7, 8.7 and 8.1 in three.
+inline int march_segments(int groups, int n) {
+    const int most = n / 8, lo = 4096 / groups + 1, hi = 12288 / groups;
+    int nseg = lo < most ? lo : most;
+    double best = 1e30;
+    for (int k = nseg; k <= hi && k <= most; ++k) {
+        const int64_t rounds = ((int64_t)groups * k + 2047) / 2048;
+        const double rows = (double)rounds * ((double)((n + k - 1) / k) + 1.5);
+        if (rows < best) {
+            best = rows;
+            nseg = k;
+        }
+    }
+    return nseg;
 }
 
 }  // namespace teno

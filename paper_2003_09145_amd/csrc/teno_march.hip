@@ -377,6 +377,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                     if (__builtin_expect(has_bnd && jn >= n, 0)) bnd_row(jn < n + 2 ? jn : n + 2, qn);
                 }
                 if (!(todo & (1u << s))) continue;
+                if (!first && pairs == kPairs) {  // no room left in this pass
+                    left |= 1u << s;
+                    continue;
+                }
                 __asm__ __volatile__("" ::: "memory");  // re-read f- per field
                 double Lr[NC];
                 left_row<ND>(R, s, Lr);
@@ -424,6 +428,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 if (first) fh[s] = combine7(v) + combine7(w);
             }
             if (__builtin_expect(pairs != 0, 0)) {
+                // A wave on a jump has several times the work of the others: it
+                // issues first from here on, so that it is not the last to end.
+                __builtin_amdgcn_s_setprio(3);
                 wave_fence();
 #pragma unroll 1
                 for (int e = lane; e - lane < 2 * pairs; e += 64) {
@@ -487,7 +494,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 }
 
 bool march_takes(const teno_grid* g, int dir, const SweepArgs& A, bool digest) {
-    return !digest && A.dump == nullptr && A.Rin != nullptr && march_grid(g, dir);
+    return !digest && A.dump == nullptr && A.Rin != nullptr && march_grid(g, dir, A.rk != 0);
 }
 
 hipError_t launch_march(const teno_grid* g, int dir, const SweepArgs& A0, hipStream_t st) {
@@ -511,22 +518,7 @@ hipError_t launch_march(const teno_grid* g, int dir, const SweepArgs& A0, hipStr
     A.ncol = march_cols(g, dir);
     A.ngrp = (int32_t)((A.ncol + 63) / 64);
     const int n = g->n[dir];
-    // Segments: 2 to 4 rounds of the 2048 waves the chip holds, the number that
-    // fills the last round best, at least 8 rows each (a segment stages 5
-    // rows more than it finishes).  384 x 384 x 256 along y: 1.65 ms with 2.25
-    // rounds, 1.52 with 3.
-    const int most = n / 8, lo = (4096 + A.ngrp - 1) / A.ngrp, hi = (8192 + A.ngrp - 1) / A.ngrp;
-    int nseg = lo < most ? lo : most;
-    double best = 0.0;
-    for (int k = nseg; k <= hi && k <= most && best < 0.97; ++k) {
-        const int64_t waves = (int64_t)A.ngrp * k;
-        const double fill = (double)waves / (double)((waves + 2047) / 2048 * 2048);
-        if (fill > best + 0.02) {
-            best = fill;
-            nseg = k;
-        }
-    }
-    A.nseg = nseg;
+    A.nseg = march_segments(A.ngrp, n);
     const dim3 grid((unsigned)(A.ngrp * A.nseg)), blk(64);
     const bool a5 = g->scheme == TENO_SCHEME_TENO5A;
     const int mode = A.s.rk >= 2 ? 2 : A.s.rk;

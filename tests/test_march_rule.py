@@ -1,5 +1,6 @@
 """Which sweeps the marching kernel takes and how it cuts their columns, from the
-library's own host code: no wave with many idle lanes."""
+library's own host code: no wave with many idle lanes, and enough waves that one on
+a jump does not end long after the others."""
 import os
 import subprocess
 
@@ -18,7 +19,11 @@ int main(int argc, char** argv) {
     memset(&g, 0, sizeof(g));
     for (int k = 0; k < 3; ++k) g.n[k] = atoi(argv[1 + k]);
     g.ndim = g.n[2] > 1 ? 3 : 2;
-    printf("%d %d\n", (int)teno::march_grid(&g, 1), g.ndim == 3 ? (int)teno::march_grid(&g, 2) : 0);
+    const bool stage = atoi(argv[4]) != 0;
+    printf("%d %d", (int)teno::march_grid(&g, 1, stage),
+           g.ndim == 3 ? (int)teno::march_grid(&g, 2, stage) : 0);
+    const int groups = (int)((teno::march_cols(&g, 1) + 63) / 64);
+    printf(" %d %d\n", groups, g.n[1] < 24 ? 0 : teno::march_segments(groups, g.n[1]));
     return 0;
 }
 '''
@@ -33,8 +38,8 @@ def rule(tmp_path_factory):
                     os.path.join(ROOT, "paper_2003_09145_amd", "csrc"), "-o", str(d / "rule"),
                     str(d / "rule.cpp")], check=True)
 
-    def ask(*n):
-        n = list(n) + [1] * (3 - len(n))
+    def ask(*n, stage=True):
+        n = list(n) + [1] * (3 - len(n)) + [int(stage)]
         out = subprocess.run([str(d / "rule"), *map(str, n)], capture_output=True, text=True, check=True)
         return [int(x) for x in out.stdout.split()]
     return ask
@@ -48,4 +53,24 @@ def rule(tmp_path_factory):
     ((12, 160003, 5), [1, 0]), ((12, 5, 160003), [0, 1]), ((6, 5, 160001), [0, 0]),
     ((5, 400, 5120), [1, 1]), ((65, 23, 160000), [0, 1])])
 def test_march_takes_full_waves(rule, n, want):
-    assert rule(*n) == want
+    assert rule(*n)[:2] == want
+
+
+@pytest.mark.parametrize("n,step,rhs", [
+    ((2048, 2048), 1, 0), ((1792, 2048), 0, 0), ((2560, 2560), 1, 1), ((2496, 2560), 1, 0)])
+def test_march_takes_right_hand_sides_later(rule, n, step, rhs):
+    assert [rule(*n)[0], rule(*n, stage=False)[0]] == [step, rhs]
+
+
+@pytest.mark.parametrize("n", [
+    (2048, 2048), (60, 60005), (61, 100003), (160000, 30), (2500000, 24), (1000000, 25), (131072, 40),
+    (256, 256, 256), (220, 220, 220), (400, 400, 400), (5, 400, 5120), (1024, 63, 200)])
+def test_march_segments(rule, n):
+    # at least 8 rows a segment, more than two rounds of 2048 waves where the rows allow it
+    _, _, groups, nseg = rule(*n)
+    rows = n[1]
+    assert 1 <= nseg <= rows // 8
+    assert groups * nseg > 4096 or nseg == rows // 8
+    cost = lambda k: -(-groups * k // 2048) * (-(-rows // k) + 1.5)
+    lo = min(4096 // groups + 1, rows // 8)
+    assert cost(nseg) == min(map(cost, range(lo, max(lo, min(rows // 8, 12288 // groups)) + 1)))
