@@ -109,12 +109,14 @@ __device__ __forceinline__ bool stage_begin(const AP& Ai, double* smem, double* 
 // kCapBlockLong: the x-sweep window of 4 chunks when lines hold n >= 252
 // cells (253 faces then span at most 2 lines: 252 + 6 + 5 = 263 cells); its
 // 31.1 KB of LDS let 5 blocks share a CU, so it is compiled for 5 waves per
-// SIMD (at most 96 VGPRs).
+// SIMD (at most 96 VGPRs); 3D TENO5-A, which would spill 8 of them, for 4 (x
+// sweep of 256^3 914 -> 929 us; 2D, with 2 spilled, 146 -> 155 us a step of 1024 x
+// 256, which stays at 5).
 constexpr int kCapBlockLong = 264;
 
 template <int ND, int DIR, int W, bool DIGEST, int CAPC, bool A5>
 __global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(ND > 1 && CAPC == kCapBlockLong ? 5 : 4))) void k_sweep(SweepArgs A) {
+__attribute__((amdgpu_waves_per_eu(ND > 1 && CAPC == kCapBlockLong && !(A5 && ND == 3) ? 5 : 4))) void k_sweep(SweepArgs A) {
     constexpr int NC = ND + 2;
     constexpr int NV = 2 * NC + ND + 2;  // f+ (NC), f- (NC), sqrt(rho), u (ND), H
     using LO = LocalOrder<ND, DIR>;
