@@ -56,13 +56,20 @@ sys.path.insert(0, ROOT)
 PEAK_FP64_TFLOPS = 78.6   # 256 CU x 4 SIMD x 16 lanes x 2 (FMA) x 2.4 GHz
 PEAK_HBM_GBS = 8000.0
 METRIC = "TENO RHS cell-updates/s (256³ FP64), % HBM roofline; batched/adjoint vs plain"
+# counter summaries: of the face-stream sweeps along every axis, and of the step
+# whose y and z sweeps are marched (a summary that holds a k_march)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sweep_3d_256_traffic.txt")
 CLOCK_FILE = os.path.join(ROOT, "profiles", "k_sweep_3d_256_clock.txt")
+MARCH_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_march_3d_256_traffic.txt")
+MARCH_CLOCK_FILE = os.path.join(ROOT, "profiles", "k_march_3d_256_clock.txt")
 # MI355X: 8 XCDs, whose GRBM_GUI_ACTIVE counts (GPU clock cycles while busy)
 # rocprofv3 sums per dispatch; the clock the published FP64 peak assumes
 N_XCD = 8
 PEAK_CLOCK_GHZ = 2.4
 SWEEP_SOURCES = ["paper_2003_09145_amd/csrc/teno_kernels.hip",
+                 "paper_2003_09145_amd/csrc/teno_march.hip",
+                 "paper_2003_09145_amd/csrc/teno_sweep.hpp",
+                 "paper_2003_09145_amd/csrc/teno_stage.hpp",
                  "paper_2003_09145_amd/csrc/teno_face.hpp",
                  "paper_2003_09145_amd/csrc/teno_device.hpp",
                  "paper_2003_09145_amd/csrc/teno_host.hpp",
@@ -146,6 +153,39 @@ def sources_sha() -> str:
 SWEEP_WAVES = {0: 4, 1: 4, 2: 8}
 
 
+def sweep_kernels(n3, axis: int):
+    """The kernels that a 3D step's sweeps along `axis` run, as (name, launches
+    per step), for line lengths of 252 and more: the march along y and z where the
+    library's march_grid takes it (its last template argument: 0 without a stage
+    update, 1 the first stage's, 2 the later ones'), else the face stream."""
+    cols = n3[0] * n3[2] if axis == 1 else n3[0] * n3[1]
+    groups = -(-cols // 64)
+    if axis == 0 or groups * n3[axis] < 160000 or 16 * cols < 15 * 64 * groups:
+        return [(f"k_sweep<3,{axis},{SWEEP_WAVES[axis]},false>", 3)]
+    if axis == 1:
+        return [("k_march<3,1,false,0>", 3)]
+    return [("k_march<3,2,false,1>", 1), ("k_march<3,2,false,2>", 2)]
+
+
+def kernel_work(short: str, n3):
+    """(axis, algorithmic bytes, literal flop, flop in the implemented order) of a
+    3D sweep kernel's launch, from its short name."""
+    axis = int(short.split(",")[1])
+    ncell, nc = math.prod(n3), 5
+    if short.startswith("k_march"):
+        mode = int(short.rstrip(">").split(",")[-1])
+        extra = ncell * nc * {0: 0, 1: 2, 2: 5}[mode]
+        return (axis, 8 * nc * ncell * (4 if mode == 2 else 3), sweep_flops_literal(n3, axis) + extra,
+                sweep_flops(3, n3, axis) + extra)
+    fused = axis == 2
+    return (axis, sweep_bytes(3, n3, axis, fused_rk=fused), sweep_flops_literal(n3, axis, fused_rk=fused),
+            sweep_flops(3, n3, axis, fused_rk=fused))
+
+
+def is_sweep(short: str) -> bool:
+    return short.startswith(("k_sweep<3", "k_march<3"))
+
+
 def match_kernel(names, kernel: str):
     """The entries of `names` that are `kernel` or an instantiation that
     extends its template arguments (k_sweep<3,2,8,false> matches
@@ -153,25 +193,33 @@ def match_kernel(names, kernel: str):
     return [k for k in names if k == kernel or k.startswith(kernel.rstrip(">") + ",")]
 
 
-def _load_counter_rows(prefix: str, kernel: str, path: str = None):
+def _load_counter_rows(prefix: str, kernel: str, paths=None):
     """The key=value fields of a committed counter summary's `prefix` line
-    for `kernel` (the traffic summary unless `path` names another), or None
+    for `kernel` (of the traffic summaries unless `paths` names others), or None
     when the sweep sources changed since it was taken."""
-    path = TRAFFIC_FILE if path is None else path
-    if not os.path.exists(path):
+    for path in (TRAFFIC_FILE, MARCH_TRAFFIC_FILE) if paths is None else paths:
+        if not os.path.exists(path):
+            continue
+        sha, vals = None, {}
+        for line in open(path):
+            if line.startswith("source_sha256:"):
+                sha = line.split(":", 1)[1].strip()
+            elif line.startswith(prefix + " "):
+                name, rest = line[len(prefix) + 1:].split(":", 1)
+                kv = dict(x.strip().split("=") for x in rest.split(","))
+                vals[name.strip()] = kv
+        names = match_kernel(vals, kernel)
+        if sha == sources_sha() and len(names) == 1:
+            return vals[names[0]]
+    return None
+
+
+def mean_over(load, kernels):
+    """The mean of load(name) over the launches of `kernels`, or None."""
+    got = [(load(k), n) for k, n in kernels]
+    if any(v is None for v, _ in got):
         return None
-    sha, vals = None, {}
-    for line in open(path):
-        if line.startswith("source_sha256:"):
-            sha = line.split(":", 1)[1].strip()
-        elif line.startswith(prefix + " "):
-            name, rest = line[len(prefix) + 1:].split(":", 1)
-            kv = dict(x.strip().split("=") for x in rest.split(","))
-            vals[name.strip()] = kv
-    names = match_kernel(vals, kernel)
-    if sha != sources_sha() or len(names) != 1:
-        return None
-    return vals[names[0]]
+    return sum(v * n for v, n in got) / sum(n for _, n in got)
 
 
 def load_traffic(kernel: str):
@@ -184,7 +232,7 @@ def load_traffic(kernel: str):
 def load_clock_ghz(kernel: str):
     """Mean GPU clock during launches of `kernel` (GRBM_GUI_ACTIVE per XCD
     over the dispatch duration) from the committed summary, or None."""
-    kv = _load_counter_rows("clock", kernel, CLOCK_FILE)
+    kv = _load_counter_rows("clock", kernel, (CLOCK_FILE, MARCH_CLOCK_FILE))
     return None if kv is None else float(kv["clock_GHz"])
 
 
@@ -245,11 +293,12 @@ def headline(args, B, W, torch):
     flops = sweep_flops_literal(n3, dom, fused_rk=fused)
     achieved = flops / (per_axis[dom] * 1e-3) / 1e12
     flops_impl = sweep_flops(3, n3, dom, fused_rk=fused)
-    # the plain (digest-free) instantiation; waves per block by axis at 256^3
-    kname = f"k_sweep<3,{dom},{SWEEP_WAVES[dom]},false>"
-    traffic = load_traffic(kname)
-    executed = load_executed_flop(kname)
-    clock = load_clock_ghz(kname)
+    # the plain (digest-free) instantiations; counters as means over their launches
+    kernels = sweep_kernels(n3, dom)
+    kname = " and ".join(k for k, _ in kernels)
+    traffic = mean_over(load_traffic, kernels)
+    executed = mean_over(load_executed_flop, kernels)
+    clock = mean_over(load_clock_ghz, kernels)
     alg_bytes = sweep_bytes(3, n3, dom, fused_rk=fused)
     roofline = {
         "bound": "alu",
@@ -877,9 +926,10 @@ def _short(name):
 
 
 def summarize_clock(d):
-    """profiles/k_sweep_3d_256_clock.txt from a GRBM_GUI_ACTIVE run under
-    d/grbm: per kernel, the busy GPU cycles per dispatch, the dispatch
-    duration and their ratio per XCD, the clock the kernel ran at."""
+    """profiles/k_march_3d_256_clock.txt (k_sweep_.. where nothing is marched)
+    from a GRBM_GUI_ACTIVE run under d/grbm: per kernel, the busy GPU cycles per
+    dispatch, the dispatch duration and their ratio per XCD, the clock the kernel
+    ran at."""
     per = {}
     for p in glob.glob(os.path.join(d, "grbm", "**", "*counter_collection.csv"), recursive=True):
         with open(p, newline="") as f:
@@ -904,14 +954,15 @@ def summarize_clock(d):
         "#",
     ]
     for k in sorted(per):
-        if not (k.startswith("k_sweep<3") or k.startswith("k_alpha<3")):
+        if not (is_sweep(k) or k.startswith("k_alpha<3")):
             continue
         v = per[k]
         cyc = sum(a for a, _ in v) / len(v)
         dur = sum(b for _, b in v) / len(v)
         lines.append(f"clock {k}: grbm_gui_active={cyc:.0f}, duration_ns={dur:.0f}, "
                      f"clock_GHz={cyc / N_XCD / dur:.3f}, dispatches={len(v)}")
-    with open(CLOCK_FILE, "w") as f:
+    marched = any(k.startswith("k_march") for k in per)
+    with open(MARCH_CLOCK_FILE if marched else CLOCK_FILE, "w") as f:
         f.write("\n".join(lines) + "\n")
     print("\n".join(lines))
 
@@ -939,7 +990,8 @@ def summarize_counters(d):
     n3 = [256] * 3
     lines = [
         "# HBM traffic and FP64 VALU counters of the 3D sweep kernels, 256^3 turbulence",
-        "# (k_sweep<3,d,W>: axis d, W waves per block; axis z carries the fused RK stage update)",
+        "# (k_sweep<3,d,W>: axis d, W waves per block; k_march<3,d,A5,M>: axis d, M = 0 without,",
+        "# 1 with the first stage's, 2 with a later stage's update)",
         "#",
         "# commands (from the repository root, after cd /tmp && export TMPDIR=/tmp; $OUT is any",
         "# output directory):",
@@ -971,17 +1023,16 @@ def summarize_counters(d):
     ]
     for k in sorted(fetch):
         sk = _short(k)
-        if not sk.startswith("k_sweep<3"):
+        if not is_sweep(sk):
             continue
         fk, nd = fetch[k]["FETCH_SIZE"]
         wk = None
         for kk, cs in write.items():
             if _short(kk) == sk and "WRITE_SIZE" in cs:
                 wk = cs["WRITE_SIZE"][0]
-        axis = int(sk.split(",")[1])
         fb = fk * 1024.0 * cal_f
         wb = (wk or 0.0) * 1024.0 * cal_w
-        alg = sweep_bytes(3, n3, axis, fused_rk=(axis == 2))
+        alg = kernel_work(sk, n3)[1]
         lines.append(f"kernel {sk}: fetch_kib={fk:.0f}, write_kib={wk or 0:.0f}, "
                      f"fetch_bytes={fb:.0f}, write_bytes={wb:.0f}, algorithmic_bytes={alg:.0f}, "
                      f"ratio={(fb + wb) / alg:.3f}, dispatches={nd}")
@@ -989,15 +1040,13 @@ def summarize_counters(d):
     lines.append("# FP64 VALU instructions per dispatch (wave-level; x64 lanes; FMA = 2 flop)")
     for k in sorted(valu):
         sk = _short(k)
-        if not sk.startswith("k_sweep<3"):
+        if not is_sweep(sk):
             continue
         cs = valu[k]
         g = lambda c: cs.get(c, (0.0, 0))[0]
         flop = 64.0 * (g("SQ_INSTS_VALU_ADD_F64") + g("SQ_INSTS_VALU_MUL_F64") +
                        g("SQ_INSTS_VALU_TRANS_F64") + 2.0 * g("SQ_INSTS_VALU_FMA_F64"))
-        axis = int(sk.split(",")[1])
-        alg = sweep_flops_literal(n3, axis, fused_rk=(axis == 2))
-        impl = sweep_flops(3, n3, axis, fused_rk=(axis == 2))
+        _, _, alg, impl = kernel_work(sk, n3)
         lines.append(f"valu {sk}: add_f64={g('SQ_INSTS_VALU_ADD_F64'):.0f}, "
                      f"mul_f64={g('SQ_INSTS_VALU_MUL_F64'):.0f}, "
                      f"fma_f64={g('SQ_INSTS_VALU_FMA_F64'):.0f}, "
@@ -1013,7 +1062,7 @@ def summarize_counters(d):
         lines.append("# selects, moves, exponent/mantissa operations and lane reads/writes)")
         for k in sorted(mix):
             sk = _short(k)
-            if not sk.startswith("k_sweep<3"):
+            if not is_sweep(sk):
                 continue
             waves = None
             for kk, cs in valu.items():
@@ -1034,17 +1083,18 @@ def summarize_counters(d):
                          f"lds={m('SQ_INSTS_LDS'):.0f}, salu={m('SQ_INSTS_SALU'):.0f}, "
                          f"wait_inst_lds={m('SQ_WAIT_INST_LDS'):.0f}, "
                          f"wait_inst_any={m('SQ_WAIT_INST_ANY'):.0f}")
-    os.makedirs(os.path.dirname(TRAFFIC_FILE), exist_ok=True)
-    with open(TRAFFIC_FILE, "w") as f:
+    path = MARCH_TRAFFIC_FILE if any("k_march" in k for k in fetch) else TRAFFIC_FILE
+    os.makedirs(os.path.dirname(path), exist_ok=True)
+    with open(path, "w") as f:
         f.write("\n".join(lines) + "\n")
     print("\n".join(lines))
 
 
-TRACE_FILE = os.path.join(ROOT, "profiles", "k_sweep_3d_256_kernel_trace.txt")
+TRACE_FILE = os.path.join(ROOT, "profiles", "k_march_3d_256_kernel_trace.txt")
 
 
 def summarize_trace(d, bench_json=None):
-    """profiles/k_sweep_3d_256_kernel_trace.txt from a rocprofv3 --kernel-trace
+    """profiles/k_march_3d_256_kernel_trace.txt from a rocprofv3 --kernel-trace
     --stats run of the headline (DIR/trace/*kernel_stats.csv) and, if given,
     the JSON line of a default bench.py run (its HIP-event sweep averages)."""
     import csv
@@ -1063,7 +1113,7 @@ def summarize_trace(d, bench_json=None):
         "python3 bench.py --no-cpu-baseline --no-extras",
         "#   python3 bench.py --summarize-trace $OUT [bench.json of a default run]",
         "# (the headline of the default bench.py run: 3 warm-up + 100 timed steps, 3 stages each,",
-        "#  so 309 launches of each per-stage kernel)",
+        "#  so 309 launches of each per-stage kernel; k_march<3, 2, ..> ends in the stage update)",
         f"source_sha256: {sources_sha()}",
         "#",
         f"{'kernel':58s} {'calls':>7s} {'avg_us':>10s} {'min_us':>10s} {'max_us':>10s} "
