@@ -716,14 +716,14 @@ static hipError_t launch_sweep(const teno_grid* g, int dir, SweepArgs A, hipStre
 // Small grids (up to kFewCells cells): the sweeps do the work around a stage
 // themselves (StageWork), ndim launches a stage and one more a step instead of
 // ndim + 2 a stage and one: a dependent launch that does next to nothing costs
-// 4 to 5 us, the same work inside a sweep 2 to 4.  Steps before and after: 128 x
-// 512 cells 97.4 -> 79.9 us, 362^2 133 -> 115, 1024 x 256 115 -> 112, 724^2 232
-// -> 221; but 1024^2 359 -> 379 (every block reads the speeds that one block
-// reads else), which keeps its own launches.
+// 4 to 5 us, the same work inside a sweep 2 to 4.  Steps with launches of their own
+// and without: 128 x 512 cells 101 / 89 us, 362^2 120 / 105, 1024 x 256 152 / 146,
+// 724^2 211 / 206; but 1024^2 323 / 335 (every block reads the speeds that one block
+// reads else), which keeps them.
 // The first sweep of up to kAllCells cells takes the speeds from the state, in
-// every block (a step of 1024 cells 43 us, of 2048 46); of more, from k_alpha's
+// every block (a step of 1024 cells 45 us, of 2048 49); of more, from k_alpha's
 // at most kFewPartials partials or from the slots that the sweep before it
-// filled (4096 and 8192 cells 46 us).
+// filled (4096 and 8192 cells 44 us; with launches of their own all four 53 to 54).
 constexpr int64_t kAllCells = 2048;
 constexpr int64_t kFewCells = 1 << 19;
 
@@ -893,8 +893,8 @@ int teno_rhs_noalloc(const teno_grid* g, const double* U, double* dUdt, const do
     const int rc = scratch_address(&S);
     if (rc != TENO_OK) return rc;
     // nothing in the scratch needs to start at zero: the reduction reads only
-    // the partials this call's k_alpha writes, and k_copy_alpha overwrites
-    // the speeds in use
+    // the partials this call's k_alpha writes, and k_copy_alpha (on a small
+    // grid the first sweep) overwrites the speeds in use
     return rhs_with_scratch(g, U, dUdt, alpha_in, alpha_out, status, nullptr, S,
                             (hipStream_t)stream);
 }

@@ -25,6 +25,13 @@ namespace teno {
 
 constexpr int kLineThreads = 576;  // of the longest line, with its six ghost cells
 
+// Doubles of LDS of an n-cell line: weights, four reduction slots per wave, the
+// staged cells, the stage state and the face fluxes.
+constexpr size_t line_lds(int n) {
+    return 24 + 4 * (kLineThreads / 64) + 9 * (size_t)(n + 6) + 3 * (size_t)n + 3 * (size_t)(n + 1);
+}
+static_assert(line_lds(kLineThreads - 6) * sizeof(double) <= 80 * 1024, "half of a CU's LDS");
+
 struct LineArgs {
     SweepArgs s;  // geometry, scheme and boundaries; U
     double* U;
@@ -159,8 +166,9 @@ __global__ __launch_bounds__(kLineThreads) void k_line(LineArgs A) {
 }
 
 // The line kernel takes 1D grids whose cells and ghost cells fit one block of
-// nine waves (two or three per SIMD, and under 64 KB of LDS), without the mask
-// digest: the gain is still 43 -> 35 us at 570 cells and shrinks with the waves
+// nine waves (two or three per SIMD, and 67.7 KB of the CU's 160 KB of LDS),
+// without the mask digest: a step of 200 cells takes 27.5 us in it and 38.6 in
+// launches of its own, of 570 cells 38 to 40 and 42; the gain shrinks with the waves
 // that share the one CU.
 bool line_takes(const teno_grid* g) {
     return g->ndim == 1 && g->n[0] + 6 <= kLineThreads && (g->flags & TENO_FLAG_MASK_DIGEST) == 0;
@@ -183,8 +191,7 @@ hipError_t launch_line(const teno_grid* g, double* U, teno_ctrl* ctrl, int nstep
     A.s.sch = scheme_of(g);
     A.s.dk = decision_consts(g, false);
     const int threads = (n + 6 + 63) / 64 * 64;
-    const size_t lds =
-        sizeof(double) * (24 + 4 * (kLineThreads / 64) + 9 * (size_t)(n + 6) + 3 * (size_t)n + 3 * (size_t)(n + 1));
+    const size_t lds = sizeof(double) * line_lds(n);
     if (g->scheme == TENO_SCHEME_TENO5A)
         hipLaunchKernelGGL(k_line<true>, dim3(1), dim3((unsigned)threads), lds, st, A);
     else

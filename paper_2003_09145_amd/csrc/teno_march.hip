@@ -9,14 +9,14 @@
 // SIMD, no barrier).  Against the face-stream sweep, whose waves share the
 // cells of one line through LDS,
 //  - every cell is staged once per segment (plus 5), with no idle lanes, every
-//    index is uniform (scalar), and the 120 LDS and 200 integer instructions
-//    per face are 68 and 30: 950 vector instructions per cell instead of 1180;
+//    index is uniform (scalar): along y of 256^3, per cell, 1010 vector
+//    instructions instead of 1190, 33 of them integer instead of 200, 68 LDS;
 //  - the next row's loads are in flight while a face is computed.
 // It is bound by instruction issue: two waves per SIMD issue one FP64
 // instruction per 5.0 cycles (measured on independent chains; 4.5 with four
 // waves), and 250 registers per lane leave no room for a third.
-// Measured per launch at 256^3 (turbulence, one box): y 0.944 -> 0.770 ms, z
-// with the stage update 1.014 -> 0.827 ms; the step 17.25 -> 15.1 ms.
+// Measured at 256^3 (turbulence, one box): step with the face stream 7.94 ms, with
+// the march 7.34; y 0.76 and z with the stage update 0.82 ms a launch.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>

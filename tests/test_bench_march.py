@@ -75,3 +75,12 @@ def test_march_summaries(tmp_path, monkeypatch):
     assert bench.mean_over(bench.load_traffic, z + [("k_march<3,1,false,0>", 3)]) is None
     open(bench.MARCH_TRAFFIC_FILE, "w").write(text.replace(bench.sources_sha(), "0" * 16))
     assert bench.mean_over(bench.load_traffic, z) is None
+
+
+def test_sweep_names_resolve_in_the_committed_summaries():
+    for path, prefix in ((bench.MARCH_TRAFFIC_FILE, "kernel "), (bench.MARCH_CLOCK_FILE, "clock ")):
+        names = [line[len(prefix):].split(":", 1)[0].strip()
+                 for line in open(path) if line.startswith(prefix)]
+        for d in range(3):
+            for k, _ in bench.sweep_kernels([256] * 3, d):
+                assert len(bench.match_kernel(names, k)) == 1, (path, k, names)
