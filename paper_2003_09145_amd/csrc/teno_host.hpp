@@ -150,13 +150,12 @@ inline int64_t march_cols(const teno_grid* g, int dir) {
 // decision pass stops all 64 columns), so the lines lie where flows full of jumps
 // (three planar ones, and the noise behind them) are about even.  Speed against
 // the face stream, jump flows (one seed each), then smooth flows:
-//  - 2D sweeps with the stage update, step of 2048^2 (65536 rows) 0.95, 1.00, 1.01,
-//    1.03, 1.03, and 1.05 to 1.07; of 1792 x 2048, below the line, 0.99 smooth; of
-//    2560^2 1.00, 1.01, 1.07, and 1.06;
-//  - without it, right-hand side of 2048^2 0.93, 0.96, 0.98, and 0.99; of 2560^2
-//    (102400 rows) 0.98, 1.03, and 1.03;
-//  - 3D, step of 220^3 (166540 rows) 0.97, 1.02, 1.04, and 1.06; of 256^3 1.00, 1.03,
-//    1.04, and 1.08; of 320^3 1.10 smooth.
+//  - 2D sweeps with the stage update: step of 1792 x 2048 (57344 rows) 0.94, 1.00,
+//    1.03, and 1.03; of 2048^2 (65536) 0.97, 1.01, 1.01, 1.03, 1.06, and 1.07;
+//  - without it: right-hand side of 2048^2 0.94, 0.95, 1.00, and 1.03; of 2304^2
+//    (82944 rows) 1.00, 1.01, 1.04, and 1.05;
+//  - 3D: step of 208^3 (140608 rows) 0.95, 0.98, 1.03, and 1.05; of 220^3 (166540) 0.99,
+//    1.04, 1.06, and 1.08; of 256^3 0.99, 1.03, 1.05, and 1.10.
 // Idle lanes cost their share, which the face-stream sweep does not pay: a sweep
 // of 3 x 60005 cells took 138 us against 13, 33 x 60011 153 / 99, 96 x 100000 481 /
 // 421, 200 x 64000 587 / 554, but 128 x 100000 477 / 557; so at most a lane in 16
@@ -165,7 +164,7 @@ inline bool march_grid(const teno_grid* g, int dir, bool stage) {
     if (dir == 0) return false;
     const int64_t cols = march_cols(g, dir), groups = (cols + 63) / 64;
     const int64_t rows = groups * g->n[dir];
-    const int64_t least = g->ndim == 3 ? 160000 : stage ? 60000 : 100000;
+    const int64_t least = g->ndim == 3 ? 160000 : stage ? 60000 : 80000;
     if (rows < least || g->n[dir] < 24) return false;
     if (16 * cols < 15 * 64 * groups) return false;
     // 32-bit lane offsets within a wave's columns and block count
@@ -173,17 +172,29 @@ inline bool march_grid(const teno_grid* g, int dir, bool stage) {
     return (63 / g->n[0] + 2) * plane < (int64_t(1) << 29) && rows < (int64_t(1) << 31);
 }
 
-// Segments of the `n` rows of each of `groups` groups of columns: at least 8 rows
-// each, in more than two rounds of the 2048 waves the chip holds, the number whose
-// rounds take the fewest rows, with 1.5 rows for the staging ahead of a segment.
-// Two rounds are 1 to 2% faster on a smooth flow, but then a wave on a jump ends
-// long after the others: steps of 256^3 with three jumps took 10.7, 9.1 and 8.7 ms
-// (three seeds) in two rounds, 9.7, 8.7 and 8.1 in three.
-inline int march_segments(int groups, int n) {
-    const int most = n / 8, lo = 4096 / groups + 1, hi = 12288 / groups;
+// Segments of the `n` rows of each of `groups` groups of columns, for waves of which
+// the chip holds 2048 at a time.  Waves are dealt out from the last segment to the
+// first, to the XCDs in turn or (by_xcd) an eighth of them to each in one stretch;
+// the segments dealt out first are twice as long as those dealt out last.  A wave on a
+// jump has several times the work of the others, and one that begins late ends
+// long after them: with two rounds of equal waves, steps of 256^3 with three
+// jumps took 10.89, 9.25 and 8.99 ms (three seeds), uneven 9.91, 8.96 and 8.28; of 2048^2
+// 1.40, 1.33 and 1.38 ms, uneven 1.30, 1.28 and 1.32.  Three rounds of equal waves do as
+// much for these flows, but stage 5 more rows half as often again: 1% of a smooth
+// 256^3 step and 1 to 4% of a 2048^2 one.
+// Of the numbers of segments for at least two rounds, with 12 rows each (equal
+// ones: three rounds, 8 rows), the one whose rounds take the fewest rows, 1.5 of them
+// for the staging ahead of a segment.
+inline MarchCut march_cut(int groups, int n, bool by_xcd) {
+    int step = by_xcd ? 8 : 1;  // each XCD its own long and short segments
+    bool uneven = groups * (int64_t)step <= 12288 && n >= 12 * step;
+    if (!uneven) step = 1;
+    const int most = n / (uneven ? 12 : 8) / step * step, hi = 12288 / groups;
+    int lo = (uneven ? 2048 : 4096) / groups + 1;
+    lo = (lo + step - 1) / step * step;
     int nseg = lo < most ? lo : most;
     double best = 1e30;
-    for (int k = nseg; k <= hi && k <= most; ++k) {
+    for (int k = nseg; k <= hi && k <= most; k += step) {
         const int64_t rounds = ((int64_t)groups * k + 2047) / 2048;
         const double rows = (double)rounds * ((double)((n + k - 1) / k) + 1.5);
         if (rows < best) {
@@ -191,7 +202,7 @@ inline int march_segments(int groups, int n) {
             nseg = k;
         }
     }
-    return nseg;
+    return {nseg, !uneven ? 1 : by_xcd ? nseg / 8 : nseg};
 }
 
 }  // namespace teno

@@ -44,6 +44,20 @@ TENO_HD int64_t xcd_logical_block(int64_t b, int64_t G) {
     return x * q + (x < r ? x : r) + b / 8;
 }
 
+// Segments of the marching sweep's columns: within every `period` segments the
+// upper half is twice as long as the lower (period 1: all alike).
+struct MarchCut {
+    int32_t nseg, period;  // period divides nseg
+};
+// First row of segment `seg` (nseg: the end) of a column of n rows.
+TENO_HD int march_row(const MarchCut& cut, int n, int seg) {
+    const int t = seg / cut.period, q = seg - t * cut.period, half = cut.period / 2;
+    const int64_t lo = (int64_t)t * cut.period * n / cut.nseg,
+                  hi = (int64_t)(t + 1) * cut.period * n / cut.nseg;
+    const int units = 2 * cut.period - half, at = q <= half ? q : 2 * q - half;
+    return (int)(lo + (hi - lo) * at / units);
+}
+
 // Cells a 64-face chunk stages (its faces' stencils, ghost cells included)
 // when every line has at least n cells: 63 faces plus 6 stencil cells, plus
 // the 5 extra ghost cells of each line boundary the chunk crosses.

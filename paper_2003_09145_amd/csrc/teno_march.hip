@@ -16,7 +16,7 @@
 // instruction per 5.0 cycles (measured on independent chains; 4.5 with four
 // waves), and 250 registers per lane leave no room for a third.
 // Measured at 256^3 (turbulence, one box): step with the face stream 7.94 ms, with
-// the march 7.34; y 0.76 and z with the stage update 0.82 ms a launch.
+// the march 7.27; y 0.75 and z with the stage update 0.81 ms a launch.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -33,7 +33,8 @@ namespace teno {
 struct MarchArgs {
     SweepArgs s;
     int64_t ncol;        // columns: every (x, z) for y, every (x, y) for z
-    int32_t ngrp, nseg;  // groups of 64 columns; segments of a column
+    int32_t ngrp;        // groups of 64 columns
+    MarchCut cut;        // segments of a column
     double cst[19];      // decision constants for the lane table (launch_march)
 };
 
@@ -198,9 +199,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     __asm__("" : "+s"(pU), "+s"(pR), "+s"(pN), "+s"(pO), "+s"(ncell), "+s"(stride));
 #endif
     const int n = Ai.s.n;
-    // rows j0 .. j0 + len - 1; a segment has at least 3 rows (host)
-    const int j0 = __builtin_amdgcn_readfirstlane((int)((int64_t)seg * n / Ai.nseg));
-    const int len = __builtin_amdgcn_readfirstlane((int)((int64_t)(seg + 1) * n / Ai.nseg)) - j0;
+    // rows j0 .. j0 + len - 1; a segment has at least 3 rows (march_cut)
+    const MarchCut seg_cut = {Ai.cut.nseg, Ai.cut.period};
+    const int j0 = __builtin_amdgcn_readfirstlane(march_row(seg_cut, n, seg));
+    const int len = __builtin_amdgcn_readfirstlane(march_row(seg_cut, n, seg + 1)) - j0;
     const double alpha = uniform(Ai.s.alpha[DIR]);
     const double gm1 = Ai.s.sch.gamma - 1.0;
 
@@ -342,6 +344,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         double fh[NC];        // reconstructed characteristic fluxes
         uint32_t done = 0;    // fields of this lane that a decision pass has settled
         uint32_t todo = (1u << NC) - 1;  // fields of this pass (uniform)
+        uint32_t rest = 0;    // fields of later passes (uniform)
         bool first = true;
         do {
             // once per pass: the left eigenvector's scalars, so that none stays
@@ -377,10 +380,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                     if (__builtin_expect(has_bnd && jn >= n, 0)) bnd_row(jn < n + 2 ? jn : n + 2, qn);
                 }
                 if (!(todo & (1u << s))) continue;
-                if (!first && pairs == kPairs) {  // no room left in this pass
-                    left |= 1u << s;
-                    continue;
-                }
                 __asm__ __volatile__("" ::: "memory");  // re-read f- per field
                 double Lr[NC];
                 left_row<ND>(R, s, Lr);
@@ -454,7 +453,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 }
                 wave_fence();
             }
-            todo = left;
+            // the two lowest fields next (a field may fill a pass by itself, and
+            // each is projected again)
+            rest |= left;
+            const uint32_t low = rest & (0u - rest), up = rest ^ low;
+            todo = low | (up & (0u - up));
+            rest ^= todo;
             first = false;
         } while (__builtin_expect(todo != 0, 0));
         // R * fh in local order, one field after the other (unit entries: plain adds)
@@ -518,8 +522,8 @@ hipError_t launch_march(const teno_grid* g, int dir, const SweepArgs& A0, hipStr
     A.ncol = march_cols(g, dir);
     A.ngrp = (int32_t)((A.ncol + 63) / 64);
     const int n = g->n[dir];
-    A.nseg = march_segments(A.ngrp, n);
-    const dim3 grid((unsigned)(A.ngrp * A.nseg)), blk(64);
+    A.cut = march_cut(A.ngrp, n, g->ndim == 2);
+    const dim3 grid((unsigned)(A.ngrp * A.cut.nseg)), blk(64);
     const bool a5 = g->scheme == TENO_SCHEME_TENO5A;
     const int mode = A.s.rk >= 2 ? 2 : A.s.rk;
     switch ((g->ndim * 4 + dir + (a5 ? 16 : 0)) * 4 + mode) {

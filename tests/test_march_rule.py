@@ -23,7 +23,13 @@ int main(int argc, char** argv) {
     printf("%d %d", (int)teno::march_grid(&g, 1, stage),
            g.ndim == 3 ? (int)teno::march_grid(&g, 2, stage) : 0);
     const int groups = (int)((teno::march_cols(&g, 1) + 63) / 64);
-    printf(" %d %d\n", groups, g.n[1] < 24 ? 0 : teno::march_segments(groups, g.n[1]));
+    const int n = g.n[1];
+    if (n >= 24) {
+        const teno::MarchCut cut = teno::march_cut(groups, n, g.ndim == 2);
+        printf(" %d %d %d", groups, cut.nseg, cut.period);
+        for (int s = 0; s <= cut.nseg; ++s) printf(" %d", teno::march_row(cut, n, s));
+    }
+    printf("\n");
     return 0;
 }
 '''
@@ -57,20 +63,33 @@ def test_march_takes_full_waves(rule, n, want):
 
 
 @pytest.mark.parametrize("n,step,rhs", [
-    ((2048, 2048), 1, 0), ((1792, 2048), 0, 0), ((2560, 2560), 1, 1), ((2496, 2560), 1, 0)])
+    ((2048, 2048), 1, 0), ((1792, 2048), 0, 0), ((2560, 2560), 1, 1), ((2304, 2304), 1, 1),
+    ((2240, 2240), 1, 0)])
 def test_march_takes_right_hand_sides_later(rule, n, step, rhs):
     assert [rule(*n)[0], rule(*n, stage=False)[0]] == [step, rhs]
 
 
 @pytest.mark.parametrize("n", [
-    (2048, 2048), (60, 60005), (61, 100003), (160000, 30), (2500000, 24), (1000000, 25), (131072, 40),
-    (256, 256, 256), (220, 220, 220), (400, 400, 400), (5, 400, 5120), (1024, 63, 200)])
-def test_march_segments(rule, n):
-    # at least 8 rows a segment, more than two rounds of 2048 waves where the rows allow it
-    _, _, groups, nseg = rule(*n)
-    rows = n[1]
-    assert 1 <= nseg <= rows // 8
-    assert groups * nseg > 4096 or nseg == rows // 8
-    cost = lambda k: -(-groups * k // 2048) * (-(-rows // k) + 1.5)
-    lo = min(4096 // groups + 1, rows // 8)
-    assert cost(nseg) == min(map(cost, range(lo, max(lo, min(rows // 8, 12288 // groups)) + 1)))
+    (2048, 2048), (1024, 4096), (60, 60005), (61, 100003), (2432, 2400), (2896, 2896), (1530, 24003),
+    (160000, 30), (2500000, 24), (1000000, 25), (131072, 40), (98304, 96), (98368, 95), (524288, 100),
+    (256, 256, 256), (220, 220, 220), (320, 320, 320), (400, 400, 400), (5, 400, 5120),
+    (1024, 63, 200), (4096, 24, 320), (4096, 25, 1000), (64, 160000, 3), (250, 36, 300)])
+def test_march_cut(rule, n):
+    _, _, groups, nseg, period, *rows = rule(*n)
+    size = [b - a for a, b in zip(rows, rows[1:])]
+    assert len(size) == nseg and rows[0] == 0 and rows[-1] == n[1]
+    # what the kernel's staging needs, and what the rule means to keep
+    assert min(size) >= 6
+    assert nseg % period == 0 and (period == 1 or n[1] >= 12 * nseg)
+    # at least two rounds of 2048 waves where the rows allow it
+    assert groups * nseg > 2048 or nseg + (8 if len(n) == 2 else 1) > n[1] // 12
+    # in 2D each XCD takes an eighth of the segments: the same rows each, the long ones last
+    if len(n) == 2 and period > 1:
+        assert nseg == 8 * period
+        eighth = [rows[(k + 1) * period] - rows[k * period] for k in range(8)]
+        assert max(eighth) - min(eighth) <= 1
+    half = period // 2
+    for k in range(0, nseg, period):
+        short, long = size[k:k + half], size[k + half:k + period]
+        if short:
+            assert max(short) < min(long) and 2 * max(short) + 2 >= max(long)
