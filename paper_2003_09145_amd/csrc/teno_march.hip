@@ -9,14 +9,14 @@
 // SIMD, no barrier).  Against the face-stream sweep, whose waves share the
 // cells of one line through LDS,
 //  - every cell is staged once per segment (plus 5), with no idle lanes, every
-//    index is uniform (scalar): along y of 256^3, per cell, 1010 vector
-//    instructions instead of 1190, 33 of them integer instead of 200, 68 LDS;
+//    index is uniform (scalar): along y of 256^3, per cell, about 1000 vector
+//    instructions instead of 1190, about 30 of them integer instead of 200;
 //  - the next row's loads are in flight while a face is computed.
 // It is bound by instruction issue: two waves per SIMD issue one FP64
 // instruction per 5.0 cycles (measured on independent chains; 4.5 with four
 // waves), and 250 registers per lane leave no room for a third.
-// Measured at 256^3 (turbulence, one box): step with the face stream 7.94 ms, with
-// the march 7.27; y 0.75 and z with the stage update 0.81 ms a launch.
+// Measured at 256^3 (turbulence, one box): step with the face stream 8.01 ms, with
+// the march 7.27; y 0.75 and z with the stage update 0.83 ms a launch.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
